@@ -86,7 +86,7 @@ struct tpcf_handle_s {
     bool self_cut = false;  // the summed self moments stop at order lmax (set by such a run)
     int couple = -1;        // this pass's contraction may skip blocks with |l1 - l2| > couple (-1: none)
     int couple_cut = -1;    // the summed blocks stop at |l1 - l2| <= couple_cut (set by tpcf_run_catalogs)
-    DevBuf d_pt_off, d_cellid, d_count, d_start, d_cursor, d_tmp, d_tmpz, d_orig, d_pf, d_pw, d_pa, d_pd, d_perm,
+    DevBuf d_pt_off, d_cellid, d_count, d_start, d_slab, d_cursor, d_tmp, d_tmpz, d_orig, d_pf, d_pw, d_pa, d_pd, d_perm,
         d_catid, d_flag, d_istart, d_icell, d_icat, d_scanw, d_catbad;
     std::vector<int32_t> cat_status;  // per catalogue of the last tpcf_run_catalogs
     std::vector<int> item_cat;       // [ncat+1] first work item of each catalogue
@@ -538,12 +538,23 @@ tpcf_status build_grid_group(tpcf_handle h, const double* d_pos, const double* d
     if (st != TPCF_OK) return st;
     const int64_t N = h->npts;
     const int64_t M = (int64_t)h->ncat * h->g.ncell;
+    // z slabs of the counting sort: with more than 64 points per cell on
+    // average, slabs of about 16 (a point's rank reads its slab, and every
+    // point adds to its slab's counter); at 64 and below the rank over a whole
+    // cell costs less than the longer scan (mock_suite grids: 9 per cell).
+    // At most 2^26 slabs.
+    h->g.zsub = 1;
+    if (N > 64 * M) h->g.zsub = (int)std::max<int64_t>(1, std::min<int64_t>(N / (16 * M), (1LL << 26) / M));
+    h->g.inv_hs = h->g.zsub * h->g.inv_h;
+    const int64_t MS = M * h->g.zsub;
     if ((st = upload(h, h->d_pt_off, h->pt_off.data(), sizeof(int64_t) * (h->ncat + 1))) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_cellid, sizeof(int) * N)) != TPCF_OK) return st;
-    if ((st = ensure(h, h->d_count, sizeof(int) * (M + 1))) != TPCF_OK) return st;
+    if ((st = ensure(h, h->d_count, sizeof(int) * (MS + 1))) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_start, sizeof(int) * (M + 1))) != TPCF_OK) return st;
-    if ((st = ensure(h, h->d_scanw, sizeof(int) * grid_scan_work_ints(M))) != TPCF_OK) return st;
-    if ((st = ensure(h, h->d_cursor, sizeof(int) * (M + 1))) != TPCF_OK) return st;
+    if (MS > M && (st = ensure(h, h->d_slab, sizeof(int) * (MS + 1))) != TPCF_OK) return st;
+    if ((st = ensure(h, h->d_scanw, sizeof(int) * grid_scan_work_ints(MS))) != TPCF_OK) return st;
+    if ((st = ensure(h, h->d_cursor, sizeof(int) * (MS + 1))) != TPCF_OK) return st;
+    int* slab = MS > M ? P<int>(h->d_slab) : P<int>(h->d_start);
     if ((st = ensure(h, h->d_tmp, sizeof(int) * N)) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_tmpz, sizeof(double) * N)) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_orig, sizeof(int) * N)) != TPCF_OK) return st;
@@ -558,20 +569,18 @@ tpcf_status build_grid_group(tpcf_handle h, const double* d_pos, const double* d
     if ((st = ensure(h, h->d_catbad, sizeof(int) * h->ncat)) != TPCF_OK) return st;
     Timer t;
     t_begin(h, 0, t);
-    HIPCHK(launch_fill_i32(P<int>(h->d_count), M + 1, 0, h->stream));
-    HIPCHK(launch_fill_i32(P<int>(h->d_cursor), M + 1, 0, h->stream));
+    HIPCHK(launch_fill_i32(P<int>(h->d_count), MS + 1, 0, h->stream));
+    HIPCHK(launch_fill_i32(P<int>(h->d_cursor), MS + 1, 0, h->stream));
     HIPCHK(launch_fill_i32(P<int>(h->d_flag), 4, 0, h->stream));
     HIPCHK(launch_fill_i32(P<int>(h->d_catbad), h->ncat, 0, h->stream));
     HIPCHK(launch_grid_assign(d_pos, d_w, N, P<int64_t>(h->d_pt_off), h->ncat, h->g, P<int>(h->d_cellid),
                               P<int>(h->d_count), P<int>(h->d_flag), P<int>(h->d_catbad), h->stream));
-    HIPCHK(launch_grid_scan(P<int>(h->d_count), M, P<int>(h->d_start), P<int>(h->d_scanw), h->stream));
-    HIPCHK(launch_grid_scatter(P<int>(h->d_cellid), N, P<int>(h->d_start), P<int>(h->d_cursor), d_pos, h->g.box,
-                               P<int>(h->d_tmp), P<double>(h->d_tmpz), h->stream));
-    HIPCHK(launch_grid_order(P<int>(h->d_cellid), N, P<int>(h->d_start), P<int>(h->d_tmp), P<double>(h->d_tmpz),
+    HIPCHK(launch_grid_scan(P<int>(h->d_count), MS, slab, P<int>(h->d_scanw), h->stream));
+    if (MS > M) HIPCHK(launch_grid_cells(slab, M, h->g.zsub, P<int>(h->d_start), h->stream));
+    HIPCHK(launch_grid_scatter(P<int>(h->d_cellid), N, h->g, slab, P<int>(h->d_cursor), d_pos, P<int>(h->d_tmp),
+                               P<double>(h->d_tmpz), h->stream));
+    HIPCHK(launch_grid_order(P<int>(h->d_cellid), N, h->g, slab, P<int>(h->d_tmp), P<double>(h->d_tmpz),
                              P<int>(h->d_orig), h->stream));
-    HIPCHK(launch_grid_fill(d_pos, d_w, N, P<int>(h->d_orig), P<int>(h->d_cellid), h->g, P<float4>(h->d_pf),
-                            P<float>(h->d_pw), P<float4>(h->d_pa), P<double4>(h->d_pd), P<int>(h->d_perm), P<int>(h->d_catid),
-                            h->stream));
     // work items of the binning pass: blocks of up to kItemPrims primaries of one cell
     const int64_t nitems_max = M + N / kItemPrims + 1;
     if ((st = ensure(h, h->d_istart, sizeof(int) * (M + 1))) != TPCF_OK) return st;
@@ -579,7 +588,9 @@ tpcf_status build_grid_group(tpcf_handle h, const double* d_pos, const double* d
     if ((st = ensure(h, h->d_icat, sizeof(int) * (h->ncat + 1))) != TPCF_OK) return st;
     HIPCHK(launch_items_count(P<int>(h->d_start), M, P<int>(h->d_cursor), h->stream));
     HIPCHK(launch_grid_scan(P<int>(h->d_cursor), M, P<int>(h->d_istart), P<int>(h->d_scanw), h->stream));
-    HIPCHK(launch_items_fill(P<int>(h->d_istart), M, P<int>(h->d_icell), h->stream));
+    HIPCHK(launch_grid_fill(d_pos, d_w, N, P<int>(h->d_orig), P<int>(h->d_cellid), h->g, P<float4>(h->d_pf),
+                            P<float>(h->d_pw), P<float4>(h->d_pa), P<double4>(h->d_pd), P<int>(h->d_perm), P<int>(h->d_catid),
+                            P<int>(h->d_start), P<int>(h->d_istart), P<int>(h->d_icell), h->stream));
     HIPCHK(launch_items_cat(P<int>(h->d_istart), h->ncat, h->g.ncell, P<int>(h->d_icat), h->stream));
     t_end(h, t);
     h->item_cat.assign(h->ncat + 1, 0);
@@ -1201,7 +1212,7 @@ void tpcf_destroy(tpcf_handle h) {
     }
     DevBuf* all[] = {&h->d_e2, &h->d_e2f, &h->d_guard, &h->d_runs, &h->d_shift_f, &h->d_goff,
                      &h->d_vol, &h->d_scale, &h->d_sign_scale, &h->d_gaunt, &h->d_pt_off, &h->d_cellid,
-                     &h->d_count, &h->d_start, &h->d_cursor, &h->d_tmp, &h->d_tmpz, &h->d_orig, &h->d_pf, &h->d_pw,
+                     &h->d_count, &h->d_start, &h->d_slab, &h->d_cursor, &h->d_tmp, &h->d_tmpz, &h->d_orig, &h->d_pf, &h->d_pw,
                      &h->d_pa, &h->d_istart, &h->d_icell, &h->d_icat, &h->d_scanw, &h->d_catbad, &h->d_pd, &h->d_perm, &h->d_catid, &h->d_flag, &h->d_list, &h->d_fix, &h->d_lcursor, &h->d_boff,
                      &h->d_cnt, &h->d_A, &h->d_subs, &h->d_catsub, &h->d_part, &h->d_pself, &h->d_G,
                      &h->d_S, &h->d_nd, &h->d_mult, &h->d_coefG, &h->d_coefS, &h->d_lflag,

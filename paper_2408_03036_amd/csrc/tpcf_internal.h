@@ -35,6 +35,8 @@ struct Grid {
     int ncell;         // nc^3
     int k;             // stencil half-width in cells (0 in single-cell mode)
     int single;        // 1: one cell, minimum image per pair
+    int zsub;          // z slabs per cell of the counting sort (1 unless cells are crowded)
+    double inv_hs;     // zsub / cell side
     int code_bits;     // bits of the stencil-offset code in a list entry
     uint32_t idx_mask; // mask of the catalogue-relative point index in a list entry
 };
@@ -56,18 +58,21 @@ hipError_t launch_grid_assign(const double* pos, const double* w, int64_t n, con
 // Exclusive scan of m counts into start[0..m]; work holds grid_scan_work_ints(m) ints.
 hipError_t launch_grid_scan(const int* count, int64_t m, int* start, int* work, hipStream_t s);
 int64_t grid_scan_work_ints(int64_t m);
-hipError_t launch_grid_scatter(const int* cellid, int64_t n, const int* start, int* cursor,
-                               const double* pos, double box, int* tmp_idx, double* tmp_key, hipStream_t s);
-hipError_t launch_grid_order(const int* cellid, int64_t n, const int* start, const int* tmp_idx,
+hipError_t launch_grid_scatter(const int* cellid, int64_t n, Grid g, const int* start, int* cursor,
+                               const double* pos, int* tmp_idx, double* tmp_key, hipStream_t s);
+hipError_t launch_grid_order(const int* cellid, int64_t n, Grid g, const int* start, const int* tmp_idx,
                              const double* tmp_key, int* orig, hipStream_t s);
+// Starts of m cells from the starts of their zsub slabs.
+hipError_t launch_grid_cells(const int* slab_start, int64_t m, int zsub, int* cell_start, hipStream_t s);
 hipError_t launch_grid_fill(const double* pos, const double* w, int64_t n, const int* orig,
                             const int* cellid, Grid g, float4* pf, float* pw, float4* pa, double4* pd,
-                            int* perm, int* catid, hipStream_t s);
+                            int* perm, int* catid, const int* cell_start, const int* item_start, int* item_cell,
+                            hipStream_t s);
 hipError_t launch_fill_i32(int* p, int64_t n, int v, hipStream_t s);
-// Work items of the binning pass: each cell's primaries in blocks of kItemPrims.
+// Work items of the binning pass: each cell's primaries in blocks of kItemPrims
+// (launch_grid_fill writes the cell of each item).
 constexpr int kItemPrims = 16;
 hipError_t launch_items_count(const int* cell_start, int64_t m, int* nitems, hipStream_t s);
-hipError_t launch_items_fill(const int* item_start, int64_t m, int* item_cell, hipStream_t s);
 hipError_t launch_items_cat(const int* item_start, int ncat, int ncell, int* item_cat, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long* p, int64_t n, unsigned long long v, hipStream_t s);
 

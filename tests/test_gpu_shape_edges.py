@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 
 from oracle import oracle as O
+from paper_2408_03036_amd import catalogs as C
 from paper_2408_03036_amd import tpcf as T
 
 pytestmark = pytest.mark.gpu
@@ -24,6 +25,38 @@ def torch():
     assert _t.cuda.is_available(), "GPU tests need a GPU"
     T.load()
     return _t
+
+
+# (box, outer edge, refinement, points): 64 points per cell on average is the
+# last size counted cell by cell; above, cells are counted in z slabs. One-cell
+# grids at 64, 65 and 1,500 points, 5^3 cells at 64 and just above.
+@pytest.mark.parametrize("box,rmax,refine,n", [(100.0, 50.0, 0, 64), (100.0, 50.0, 0, 65), (100.0, 50.0, 0, 1500),
+                                               (200.0, 40.0, 1, 8000), (200.0, 40.0, 1, 8001)])
+@pytest.mark.parametrize("lattice", [False, True])
+def test_crowded_cells_in_slabs(torch, box, rmax, refine, n, lattice):
+    """The slabs keep the order by z and input index inside a cell: a crowded
+    catalogue alone and in a batch whose average is far below the threshold
+    (no slabs) gives the same bits, and exact counts at lmax 0. The lattice has
+    many points of equal z, and points outside the box to be wrapped."""
+    pos = C.dyadic_lattice(n, box, 4, 5) - box if lattice else C.poisson(n, box, 6)
+    tiny = [C.poisson(3, box, 700 + i) for i in range(60)]
+    sizes = [n] + [3] * len(tiny)
+    edges = np.linspace(0.1 * rmax, rmax, 5)
+    say(f"  slabs: n={n} box={box} refine={refine} lattice={lattice}")
+    P = torch.from_numpy(pos).cuda()
+    B = torch.from_numpy(np.vstack([pos] + tiny)).cuda()
+    mults = O.all_multipoles(2, 2)
+    h = T.Handle(box, edges, 2, precision=T.PREC_FP32, grid_refine=refine)
+    one = h.run_catalogs([n], [n], P, None, mults).cpu().numpy()
+    many = h.run_catalogs(sizes, sizes, B, None, mults).cpu().numpy()
+    h.close()
+    assert np.array_equal(one[0], many[0])
+    h = T.Handle(box, edges, 0, precision=T.PREC_FP32, grid_refine=refine)
+    got = h.run_catalogs([n], [n], P, None, [(0, 0, 0)]).cpu().numpy()
+    h.close()
+    ref, _, _ = O.run(pos, box, edges, 0, [(0, 0, 0)])
+    # integer counts: only the final FP64 normalisation rounds
+    assert np.abs(got[0] - ref).max() <= 1e-12 * np.abs(ref).max()
 
 
 # n = sum k^2 unknowns: 1, 5 and 30 (one panel of 32 columns, part filled), 55,
