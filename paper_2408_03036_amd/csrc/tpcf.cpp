@@ -95,7 +95,7 @@ struct tpcf_handle_s {
     std::vector<int64_t> sub_start;  // global subchunks (sorted index of first primary), + end
     std::vector<int> cat_sub;        // [ncat+1]
     std::vector<Chunk> chunks;
-    int64_t kc = 4096;  // primaries per subchunk (the self-moment kernel stages at most 4096 weights)
+    int64_t kc = 4096;  // most primaries per subchunk (the self-moment kernel stages at most 4096 weights)
     int uniform = 0;      // bins equally spaced in r
     float inv_dr = 0.f;   // 1 / bin width (uniform bins)
     float delta = 0.f;    // FP32 guard band in units of the bin width
@@ -607,9 +607,31 @@ size_t list_elem_bytes(tpcf_handle h) {
     return (h->unit_w && h->lmax <= 10) ? 2 * sizeof(float) : sizeof(float4);
 }
 
-// Splits every catalogue into subchunks of kc primaries and groups whole
-// subchunks into chunks whose a_lm operand and hit lists fit the workspace share.
-tpcf_status plan_chunks(tpcf_handle h) {
+// Primaries per subchunk of a catalogue of n points: a power of two from 256 to
+// kc, about n / (2 share) at least. A workgroup of the contraction sums one
+// subchunk of one m, so a catalogue needs a few dozen subchunks to fill the
+// chip, while a workgroup's first load, its tables and its partial sums are
+// paid once per subchunk. share 32 for the FP64, FP32 and isotropic kernels,
+// which run several workgroups per CU (FP32, 30,011 primaries at lmax 13 and
+// 7 bins: 135 us against 370 us with kc; FP64, 1e5 at lmax 10: 0.38 against
+// 0.63 ms); share 16 for the split-BF16 kernel, which has one workgroup
+// per CU and long steps (64 catalogues of 5e4 to 3e5 points, lmax 10: the
+// stage takes 0.9 ms more with share 32, the same with 16 and with kc
+// throughout; 2,000 primaries at lmax 4: 14 us against 65 us with one
+// subchunk).
+// The length depends on the handle and the catalogue alone, so that batched
+// and single runs sum in the same order, and is a multiple of every group of
+// primaries that the contractions sum in FP32.
+int64_t subchunk_of(int64_t n, int64_t kc, int64_t share) {
+    int64_t k = 256;
+    while (k < kc && 2 * share * k <= n) k *= 2;
+    return k;
+}
+
+// Splits every catalogue into subchunks and groups whole subchunks into
+// chunks whose a_lm operand and hit lists fit the workspace share. fine:
+// subchunks by the size of the catalogue, else all of kc primaries.
+tpcf_status plan_chunks_of(tpcf_handle h, bool fine) {
     const int64_t N = h->npts;
     const size_t elem = h->fp64 ? 8 : 4;
     const int64_t per_prim = (int64_t)h->nb * h->NV * (int64_t)elem;
@@ -649,9 +671,13 @@ tpcf_status plan_chunks(tpcf_handle h) {
     h->chunk_cap = cap;
     h->sub_start.clear();
     h->cat_sub.assign(h->ncat + 1, 0);
+    const bool split = (h->mode == TPCF_PREC_MIXED_BF16X3 || h->mode == TPCF_PREC_MIXED_BF16X6) &&
+                       !(h->cfg.flags & TPCF_F_ISOTROPIC);
+    const int64_t share = split ? 16 : 32;
     for (int c = 0; c < h->ncat; ++c) {
         h->cat_sub[c] = (int)h->sub_start.size();
-        for (int64_t p = h->pt_off[c]; p < h->pt_off[c + 1]; p += h->kc) h->sub_start.push_back(p);
+        const int64_t kc = fine ? subchunk_of(h->pt_off[c + 1] - h->pt_off[c], h->kc, share) : h->kc;
+        for (int64_t p = h->pt_off[c]; p < h->pt_off[c + 1]; p += kc) h->sub_start.push_back(p);
     }
     h->cat_sub[h->ncat] = (int)h->sub_start.size();
     h->sub_start.push_back(N);
@@ -729,6 +755,13 @@ tpcf_status plan_chunks(tpcf_handle h) {
     const int sw = h->nb * (2 * h->lmax + 2);
     if ((st = ensure(h, h->d_pself, sizeof(double) * nsub * sw)) != TPCF_OK) return st;
     return TPCF_OK;
+}
+
+// A workspace with no room for the partial sums of the finer subchunks gets
+// the coarse ones.
+tpcf_status plan_chunks(tpcf_handle h) {
+    const tpcf_status st = plan_chunks_of(h, true);
+    return st == TPCF_ERR_ALLOC ? plan_chunks_of(h, false) : st;
 }
 
 // Pair pass of one chunk: binning, fix-up of the primaries whose predicted

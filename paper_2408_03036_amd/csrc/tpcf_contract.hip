@@ -36,373 +36,367 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 
-__device__ inline unsigned short bf16_bits_rn(float x) {
-    uint32_t u = __float_as_uint(x);
-    // round to nearest even (inputs are finite)
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (unsigned short)(u >> 16);
-}
-__device__ inline float bf16_to_float(unsigned short h) { return __uint_as_float((uint32_t)h << 16); }
+// ---------------------------------------------------------------- FP64 and FP32
+// Work split of the FP64 and FP32 contractions. A workgroup covers one
+// (subchunk, m) and up to kWaves * TPW upper-triangle tiles. The operand is
+// staged in units: kUnit consecutive primaries of one part (re or im) of every
+// column. A step stages as many consecutive units as the threads' registers
+// hold (`units`, set per m from the column count, so that the narrow high-m
+// operands take few steps), into one of two LDS buffers: the loads of step
+// s + 1 are issued before the MFMAs of step s and stored after them. All loads
+// are unconditional and in bounds (the operand ends with 8 elements of
+// padding; an idle item, or one past the subchunk, reads the start of its row
+// or of the buffer), elements that are not the unit's primaries are zeroed
+// when stored. The MFMA loop has no branch (a wave's tile count is a template
+// parameter). Columns are l-major, and a batched run forms only the tiles
+// its multipoles couple, as in the split-BF16 kernel below.
+constexpr int kUnit = 32;
+constexpr int kGroup = 4;                 // primaries of a staged item
+constexpr int kUnitItems = kUnit / kGroup;
 
-template <int MODE> struct Cfg;
-template <> struct Cfg<0> { static constexpr int TS = 16, KS = 32, TPW = 8, KSTEP = 4; };
-template <> struct Cfg<1> { static constexpr int TS = 32, KS = 32, TPW = 4, KSTEP = 2; };
-template <> struct Cfg<2> { static constexpr int TS = 32, KS = 64, TPW = 4, KSTEP = 16; };
-template <> struct Cfg<3> { static constexpr int TS = 32, KS = 32, TPW = 4, KSTEP = 16; };
-
-__device__ inline void tile_of(int t, int nt, int& ti, int& tj) {
-    // t-th upper-triangle tile in row-major order
-    int r = 0, rem = t;
-    while (rem >= nt - r) { rem -= nt - r; ++r; }
-    ti = r;
-    tj = r + rem;
-}
-
-template <int MODE>
-__global__ void __launch_bounds__(256) k_contract(ContractArgs a) {
-    using C = Cfg<MODE>;
-    constexpr int TS = C::TS, KS = C::KS, TPW = C::TPW;
-    extern __shared__ unsigned char smem[];
-    const int s = blockIdx.x;
-    const int m = blockIdx.y;
-    const int lmax = a.lmax, nb = a.nb;
-    const int nl = lmax - m + 1;
-    const int K = nb * nl;
+// Tiles of the upper triangle (TS columns each, l-major: column c holds
+// l - m = c / nb of bin c % nb) whose columns couple some l1, l2 with
+// |l1 - l2| <= lcouple, in row-major order: a wave takes the (first + stride q)-th
+// of them, q < N; returns how many it has (they come first), and all[0] the
+// number of needed tiles. Along a row of tiles the smallest l distance only
+// grows, so a row ends at its first tile past the limit.
+template <int TS, int N>
+__device__ __forceinline__ int pick_tiles(int K, int nb, int lcouple, int first, int stride, int (&ti)[N],
+                                          int (&tj)[N], int& all) {
     const int nt = (K + TS - 1) / TS;
-    const int ntiles = nt * (nt + 1) / 2;
-    const int t0 = blockIdx.z * 4 * TPW;
-    if (t0 >= ntiles) return;
-    const int parts = m == 0 ? 1 : 2;
-    const int NV = n_values(lmax);
-    const int voff = value_offset(lmax, m);
-    const int wave = threadIdx.x >> 6;
-    const int lane = threadIdx.x & 63;
-    const int64_t pa = a.sub_start[s], pb = a.sub_start[s + 1];
-    const int ncol = nt * TS;
-
-    int ti[TPW], tj[TPW];
-    bool tv[TPW];
+    int mine = 0;
+    all = 0;
 #pragma unroll
-    for (int q = 0; q < TPW; ++q) {
-        const int t = t0 + wave + 4 * q;
-        tv[q] = t < ntiles;
-        tile_of(tv[q] ? t : 0, nt, ti[q], tj[q]);
-    }
-
-    // LDS: X[col][k] (and weighted copy), stride KSP elements
-    constexpr int KSP = MODE >= 2 ? KS + 8 : KS + 1;
-    constexpr int NPC = MODE == 3 ? 3 : 2;  // BF16 pieces per value
-    typedef typename std::conditional<MODE == 0, double, float>::type TA;
-    // FP32 MFMA accumulators are emptied into FP64 registers after every
-    // K-step (KS primaries), so single precision only ever sums a few dozen
-    // products before the FP64 sum takes over.
-    f32x16 acc32[TPW];
-    f64x4 acc64[TPW];
-    double accd[TPW][MODE == 0 ? 1 : 16];
+    for (int q = 0; q < N; ++q) ti[q] = tj[q] = 0;
+    for (int r = 0; r < nt; ++r) {
+        const int lhi = (min(K, r * TS + TS) - 1) / nb;
+        for (int c = r; c < nt; ++c) {
+            if (c * TS / nb - lhi > lcouple) break;
 #pragma unroll
-    for (int q = 0; q < TPW; ++q) {
-        acc32[q] = (f32x16)0.0f;
-        acc64[q] = (f64x4)0.0;
-#pragma unroll
-        for (int r = 0; r < (MODE == 0 ? 1 : 16); ++r) accd[q][r] = 0.0;
-    }
-    double* wts = reinterpret_cast<double*>(smem);  // KS weights
-    unsigned char* xbase = smem + KS * sizeof(double);
-
-    for (int64_t p0 = pa; p0 < pb; p0 += KS) {
-        const int kk_valid = (int)min((int64_t)KS, pb - p0);
-        for (int part = 0; part < parts; ++part) {
-            __syncthreads();
-            if (threadIdx.x < KS) {
-                const int k = threadIdx.x;
-                wts[k] = (k < kk_valid) ? a.pd[a.p_begin + p0 + k].w : 0.0;
-            }
-            __syncthreads();
-            // stage columns
-            for (int idx = threadIdx.x; idx < ncol * KS; idx += 256) {
-                const int c = idx / KS, k = idx - c * KS;
-                TA v = (TA)0;
-                if (c < K && k < kk_valid) {
-                    const int b = c / nl, lp = c - b * nl;
-                    const int64_t row = (int64_t)b * NV + voff + part * nl + lp;
-                    v = reinterpret_cast<const TA*>(a.A)[row * a.ldA + p0 + k];
+            for (int q = 0; q < N; ++q)
+                if (all == first + stride * q) {
+                    ti[q] = r;
+                    tj[q] = c;
+                    mine = q + 1;
                 }
-                if constexpr (MODE >= 2) {
-                    // pieces of x in planes 0..NPC-1, pieces of w x in planes NPC..2NPC-1
-                    unsigned short* xp = reinterpret_cast<unsigned short*>(xbase);
-                    const int plane = ncol * KSP;
-                    float r = (float)v;
-#pragma unroll
-                    for (int q = 0; q < NPC; ++q) {
-                        const unsigned short hq = bf16_bits_rn(r);
-                        xp[q * plane + c * KSP + k] = hq;
-                        r -= bf16_to_float(hq);
-                    }
-                    if (!a.unit_weights) {
-                        float rw = (float)((double)v * wts[k]);
-#pragma unroll
-                        for (int q = 0; q < NPC; ++q) {
-                            const unsigned short hq = bf16_bits_rn(rw);
-                            xp[(NPC + q) * plane + c * KSP + k] = hq;
-                            rw -= bf16_to_float(hq);
-                        }
-                    }
-                } else {
-                    TA* X = reinterpret_cast<TA*>(xbase);
-                    X[c * KSP + k] = v;
-                }
-            }
-            __syncthreads();
-            if constexpr (MODE == 0) {
-                const double* X = reinterpret_cast<const double*>(xbase);
-                const int i = lane & 15, kg = lane >> 4;
-                for (int k0 = 0; k0 < KS; k0 += 4) {
-                    const double wv = a.unit_weights ? 1.0 : wts[k0 + kg];
-#pragma unroll
-                    for (int q = 0; q < TPW; ++q) {
-                        if (!tv[q]) continue;
-                        const double av = X[(ti[q] * TS + i) * KSP + k0 + kg] * wv;
-                        const double bv = X[(tj[q] * TS + i) * KSP + k0 + kg];
-                        acc64[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc64[q], 0, 0, 0);
-                    }
-                }
-            } else if constexpr (MODE == 1) {
-                const float* X = reinterpret_cast<const float*>(xbase);
-                const int i = lane & 31, kg = lane >> 5;
-                for (int k0 = 0; k0 < KS; k0 += 2) {
-                    const float wv = a.unit_weights ? 1.0f : (float)wts[k0 + kg];
-#pragma unroll
-                    for (int q = 0; q < TPW; ++q) {
-                        if (!tv[q]) continue;
-                        const float av = X[(ti[q] * TS + i) * KSP + k0 + kg] * wv;
-                        const float bv = X[(tj[q] * TS + i) * KSP + k0 + kg];
-                        acc32[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc32[q], 0, 0, 0);
-                    }
-                }
-            } else {
-                const unsigned short* xp = reinterpret_cast<const unsigned short*>(xbase);
-                const int plane = ncol * KSP;
-                const unsigned short* wp = a.unit_weights ? xp : xp + NPC * plane;
-                const int i = lane & 31, kg = lane >> 5;
-                for (int k0 = 0; k0 < KS; k0 += 16) {
-#pragma unroll
-                    for (int q = 0; q < TPW; ++q) {
-                        if (!tv[q]) continue;
-                        const int ra = (ti[q] * TS + i) * KSP + k0 + 8 * kg;
-                        const int rb = (tj[q] * TS + i) * KSP + k0 + 8 * kg;
-                        bf16x8 ap[NPC], bp[NPC];
-#pragma unroll
-                        for (int u = 0; u < NPC; ++u) {
-                            ap[u] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8*>(wp + u * plane + ra));
-                            bp[u] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8*>(xp + u * plane + rb));
-                        }
-                        // products of pieces u, v with u + v <= NPC - 1: hi.hi, hi.lo, lo.hi
-                        // for two pieces; hi.hi, hi.mid, mid.hi, mid.mid, hi.lo, lo.hi for three
-#pragma unroll
-                        for (int u = 0; u < NPC; ++u)
-#pragma unroll
-                            for (int v2 = 0; v2 < NPC; ++v2)
-                                if (u + v2 <= NPC - 1)
-                                    acc32[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ap[u], bp[v2], acc32[q], 0, 0, 0);
-                    }
-                }
-            }
-        }
-        if constexpr (MODE != 0) {
-#pragma unroll
-            for (int q = 0; q < TPW; ++q) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) accd[q][r] += (double)acc32[q][r];
-                acc32[q] = (f32x16)0.0f;
-            }
+            ++all;
         }
     }
-    // write the partial tiles
-    const int64_t sg = (int64_t)(a.sub_base + s);
-#pragma unroll
-    for (int q = 0; q < TPW; ++q) {
-        if (!tv[q]) continue;
-        if constexpr (MODE == 0) {
-            const int j = lane & 15;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int i = (lane >> 4) + 4 * r;
-                const int ci = ti[q] * TS + i, cj = tj[q] * TS + j;
-                if (ci < K && cj < K)
-                    a.part64[sg * a.gsize + a.goff[m] + (int64_t)ci * K + cj] = acc64[q][r];
-            }
-        } else {
-            const int j = lane & 31;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int i = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-                const int ci = ti[q] * TS + i, cj = tj[q] * TS + j;
-                if (ci < K && cj < K)
-                    a.part64[sg * a.gsize + a.goff[m] + (int64_t)ci * K + cj] = accd[q][r];
-            }
-        }
+    return mine;
+}
+
+// Writes entry (ci, cj) of an upper-triangle tile (ti, tj) once per unordered
+// column pair, at the upper-triangle position of the bin-major order
+// b (lmax - m + 1) + l - m that the reduction, finalize and export read.
+template <bool LMAJOR = true>
+__device__ __forceinline__ void put_entry(double* G, int K, int nb, int nl, int ti, int tj, int ci, int cj,
+                                          double v) {
+    if (ci < K && cj < K && (ti < tj || ci <= cj)) {
+        const int oi = LMAJOR ? (ci % nb) * nl + ci / nb : ci, oj = LMAJOR ? (cj % nb) * nl + cj / nb : cj;
+        G[(int64_t)min(oi, oj) * K + max(oi, oj)] = v;
     }
 }
 
-// ---------------------------------------------------------------- FP64, double-buffered
-// The FP64 contraction of k_contract<0> (16x16 tiles, eight per wavefront,
-// 16x16x4 FP64 MFMA, the same LDS layout) with the staging of the
-// split-BF16 kernel. Per step (KS primaries of one part) every thread owns up
-// to kF64IPT items of four consecutive primaries of one column. Their loads
-// for step st + 1 (two 16-byte loads per item, unconditional and in bounds:
-// the operand buffer ends with 8 elements of padding, and an idle item or one
-// past the step's primaries reads the start of the buffer or of its row) are
-// issued before the MFMAs of step st and stored into the other LDS buffer
-// after them, with the elements that are not the step's primaries zeroed.
-// Used when the items of the widest m fit the workgroup and two buffers fit
-// LDS; k_contract<0> covers the other shapes.
-constexpr int kF64IPT = 4;
+// The thread's staged items: flat column it / kUnitItems of the step (unit by
+// unit, ncol columns each), primaries k4 .. k4 + 3 of its unit.
+template <int IPT, bool LMAJOR = true>
+struct Items {
+    int row[IPT];   // operand row of part 0, or -1: a column past K
+    int unit[IPT];  // unit of the step, or -1: no item
+    int col[IPT];
+    int k4;
+    __device__ __forceinline__ Items(int tid, int threads, int units, int ncol, int K, int nb, int NV, int voff) {
+        k4 = (tid % kUnitItems) * kGroup;
+#pragma unroll
+        for (int u = 0; u < IPT; ++u) {
+            const int fc = tid / kUnitItems + u * (threads / kUnitItems);
+            unit[u] = fc < units * ncol ? fc / ncol : -1;
+            col[u] = fc % ncol;
+            const int nl = K / nb;
+            const int b = LMAJOR ? col[u] % nb : col[u] / nl, lp = LMAJOR ? col[u] / nb : col[u] % nl;
+            row[u] = unit[u] >= 0 && col[u] < K ? b * NV + voff + lp : -1;
+        }
+    }
+};
 
-__host__ __device__ constexpr size_t f64db_lds(int ncol) {
-    return 2 * (size_t)(Cfg<0>::KS + ncol * (Cfg<0>::KS + 1)) * sizeof(double);
+// Units of a step: as many as fill cols flat columns, at most 8.
+__host__ __device__ inline int step_units(int ncol, int cols) { return min(8, max(1, cols / ncol)); }
+
+// FP64: 16x16x4 MFMA, eight wavefronts with up to four tiles each. A lane
+// group takes eight consecutive primaries of a unit (the order of the sum is
+// free), so an operand fragment is one 16-byte LDS read for two MFMAs; a row
+// stride of 34 doubles keeps those reads free of bank conflicts.
+// Bound: the operand's bytes (1.14 GB for 1e5 primaries at lmax 10, 10 bins:
+// 0.24 ms) and, close to it, the MFMAs (0.16 ms); it takes 0.38 ms, 0.63 ms
+// with subchunks of 4096. Eight tiles a wave, a branch per tile in the MFMA
+// loop, 8-byte LDS reads, one unit per step and subchunks of 4096 took 1.15 ms.
+constexpr int kF64Waves = 8, kF64TPW = 4, kF64Stride = kUnit + 2;
+
+__host__ __device__ constexpr size_t f64_lds(int flat_cols, int units, int nbuf) {
+    return (size_t)nbuf * ((size_t)flat_cols * kF64Stride + (size_t)units * kUnit) * sizeof(double);
 }
 
-template <bool W>
-__global__ void __launch_bounds__(256) k_contract_f64(ContractArgs a) {
-    using C = Cfg<0>;
-    constexpr int TS = C::TS, KS = C::KS, TPW = C::TPW, KSP = KS + 1;
+template <bool W, int IPT>
+__global__ void __launch_bounds__(64 * kF64Waves) k_contract_f64(ContractArgs a, int cols, int nbuf) {
+    constexpr int TS = 16, TPW = kF64TPW, KSP = kF64Stride;
     extern __shared__ unsigned char smem[];
-    const int s = blockIdx.x;
-    const int m = blockIdx.y;
-    const int lmax = a.lmax, nb = a.nb;
-    const int nl = lmax - m + 1;
-    const int K = nb * nl;
-    const int nt = (K + TS - 1) / TS;
-    const int ntiles = nt * (nt + 1) / 2;
-    const int t0 = blockIdx.z * 4 * TPW;
-    if (t0 >= ntiles) return;
+    const int s = blockIdx.x, m = blockIdx.y;
+    const int nb = a.nb, nl = a.lmax - m + 1, K = nb * nl;
+    const int ncol = (K + TS - 1) / TS * TS;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    int ti[TPW], tj[TPW], all;
+    const int t0 = blockIdx.z * kF64Waves * TPW;
+    const int nq = pick_tiles<TS>(K, nb, a.lcouple, t0 + wave, kF64Waves, ti, tj, all);
+    if (t0 >= all) return;
     const int parts = m == 0 ? 1 : 2;
-    const int NV = n_values(lmax);
-    const int voff = value_offset(lmax, m);
-    const int wave = threadIdx.x >> 6;
-    const int lane = threadIdx.x & 63;
+    const int units = step_units(ncol, cols);
     const int64_t pa = a.sub_start[s], pb = a.sub_start[s + 1];
-    const int ncol = nt * TS;
-
-    int ti[TPW], tj[TPW];
-    bool tv[TPW];
-#pragma unroll
-    for (int q = 0; q < TPW; ++q) {
-        const int t = t0 + wave + 4 * q;
-        tv[q] = t < ntiles;
-        tile_of(tv[q] ? t : 0, nt, ti[q], tj[q]);
-    }
-    f64x4 acc64[TPW];
-#pragma unroll
-    for (int q = 0; q < TPW; ++q) acc64[q] = (f64x4)0.0;
-
-    // per buffer: KS weights, then X[col][k] with stride KSP
-    const int bufd = KS + ncol * KSP;
-    double* lds = reinterpret_cast<double*>(smem);
+    const int total = (int)((pb - pa + kUnit - 1) / kUnit) * parts;  // units of the subchunk
+    const int nsteps = (total + units - 1) / units;
+    const Items<IPT> it(threadIdx.x, 64 * kF64Waves, units, ncol, K, nb, n_values(a.lmax), value_offset(a.lmax, m));
     const double* A = reinterpret_cast<const double*>(a.A);
-    constexpr int groups = KS / 4;
-    const int nitems = ncol * groups;
-    const int nkst = (int)((pb - pa + KS - 1) / KS);
-    const int nsteps = nkst * parts;
-
-    // the thread's items: column c, primaries k4 .. k4+3 of the step
-    int64_t irow[kF64IPT];
-    int ioff[kF64IPT], ik4[kF64IPT];
-    bool iok[kF64IPT], istore[kF64IPT];
-#pragma unroll
-    for (int u = 0; u < kF64IPT; ++u) {
-        const int it = threadIdx.x + u * 256;
-        const int c = it / groups, k4 = (it - c * groups) * 4;
-        const int b = c / nl, lp = c - b * nl;
-        istore[u] = it < nitems;
-        iok[u] = it < nitems && c < K;
-        ik4[u] = k4;
-        ioff[u] = c * KSP + k4;
-        irow[u] = ((int64_t)b * NV + voff + lp) * a.ldA;
-    }
-    const int64_t part_stride = (int64_t)nl * a.ldA;
+    double* lds = reinterpret_cast<double*>(smem);
+    const int bufsz = units * (ncol * KSP + kUnit);
 
     struct Stage {
-        double x[kF64IPT][4];
+        double2 x[IPT][2];
         double w;
     };
     auto load = [&](int st, Stage& R) {
-        const int part = st % parts;
-        const int64_t p0 = pa + (int64_t)(st / parts) * KS;
-        const int kv = (int)min((int64_t)KS, pb - p0);
 #pragma unroll
-        for (int u = 0; u < kF64IPT; ++u) {
-            const int kk = ik4[u] < kv ? ik4[u] : 0;
-            const double* src = A + (iok[u] ? irow[u] + part * part_stride + p0 + kk : 0);
-            double2 v0, v1;
-            __builtin_memcpy(&v0, src, 16);
-            __builtin_memcpy(&v1, src + 2, 16);
-            R.x[u][0] = v0.x;
-            R.x[u][1] = v0.y;
-            R.x[u][2] = v1.x;
-            R.x[u][3] = v1.y;
+        for (int u = 0; u < IPT; ++u) {
+            const int g = st * units + max(it.unit[u], 0);
+            const int64_t p0 = pa + (int64_t)(g / parts) * kUnit;
+            const bool in = it.row[u] >= 0 && g < total;
+            const double* src =
+                A + (in ? (int64_t)(it.row[u] + (g % parts) * nl) * a.ldA + p0 + (p0 + it.k4 < pb ? it.k4 : 0) : 0);
+            __builtin_memcpy(&R.x[u][0], src, 16);
+            __builtin_memcpy(&R.x[u][1], src + 2, 16);
         }
         if constexpr (W) {
-            // thread k (< KS) stages the weight of primary k of the step
-            const int k = threadIdx.x % KS;
-            R.w = a.pd[a.p_begin + p0 + (k < kv ? k : 0)].w;
+            // thread t stages the weight of primary t % kUnit of unit t / kUnit
+            const int64_t p = pa + (int64_t)((st * units + (int)threadIdx.x / kUnit) / parts) * kUnit + threadIdx.x % kUnit;
+            R.w = a.pd[a.p_begin + (p < pb ? p : pa)].w;
         }
     };
     auto store = [&](int st, int buf, const Stage& R) {
-        double* base = lds + buf * bufd;
-        const int64_t p0 = pa + (int64_t)(st / parts) * KS;
-        const int kv = (int)min((int64_t)KS, pb - p0);
+        double* base = lds + buf * bufsz;
         if constexpr (W) {
-            if (threadIdx.x < KS) base[threadIdx.x] = (int)threadIdx.x < kv ? R.w : 0.0;
+            if ((int)threadIdx.x < units * kUnit) base[units * ncol * KSP + threadIdx.x] = R.w;
         }
-        double* X = base + KS;
 #pragma unroll
-        for (int u = 0; u < kF64IPT; ++u) {
-            if (!istore[u]) continue;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const bool ok = iok[u] && ik4[u] + e < kv;
-                X[ioff[u] + e] = ok ? R.x[u][e] : 0.0;
-            }
+        for (int u = 0; u < IPT; ++u) {
+            if (it.unit[u] < 0) continue;
+            const int g = st * units + it.unit[u];
+            const int kv = it.row[u] >= 0 && g < total
+                               ? (int)min((int64_t)kUnit, pb - pa - (int64_t)(g / parts) * kUnit) - it.k4 : 0;
+            double2 v0 = R.x[u][0], v1 = R.x[u][1];
+            v0.x = kv > 0 ? v0.x : 0.0;
+            v0.y = kv > 1 ? v0.y : 0.0;
+            v1.x = kv > 2 ? v1.x : 0.0;
+            v1.y = kv > 3 ? v1.y : 0.0;
+            double2* dst = reinterpret_cast<double2*>(base + (it.unit[u] * ncol + it.col[u]) * KSP + it.k4);
+            dst[0] = v0;
+            dst[1] = v1;
         }
     };
+    f64x4 acc[TPW];
+#pragma unroll
+    for (int q = 0; q < TPW; ++q) acc[q] = (f64x4)0.0;
     const int i = lane & 15, kg = lane >> 4;
-    auto compute = [&](int buf) {
-        const double* base = lds + buf * bufd;
-        const double* X = base + KS;
-        for (int k0 = 0; k0 < KS; k0 += 4) {
-            const double wv = W ? base[k0 + kg] : 1.0;
+    auto mma = [&](auto nqc, int buf) {
+        constexpr int NQ = decltype(nqc)::value;
+        const double* base = lds + buf * bufsz;
+        for (int u = 0; u < units; ++u) {
+            const double* X = base + u * ncol * KSP + 8 * kg;
+            const double* wt = base + units * ncol * KSP + u * kUnit + 8 * kg;
 #pragma unroll
-            for (int q = 0; q < TPW; ++q) {
-                if (!tv[q]) continue;
-                const double av = X[(ti[q] * TS + i) * KSP + k0 + kg] * wv;
-                const double bv = X[(tj[q] * TS + i) * KSP + k0 + kg];
-                acc64[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc64[q], 0, 0, 0);
+            for (int k = 0; k < 8; k += 2) {
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    double2 av = *reinterpret_cast<const double2*>(X + (ti[q] * TS + i) * KSP + k);
+                    const double2 bv = *reinterpret_cast<const double2*>(X + (tj[q] * TS + i) * KSP + k);
+                    if constexpr (W) {
+                        av.x *= wt[k];
+                        av.y *= wt[k + 1];
+                    }
+                    acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.x, bv.x, acc[q], 0, 0, 0);
+                    acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av.y, bv.y, acc[q], 0, 0, 0);
+                }
             }
         }
     };
-
+    auto compute = [&](int buf) {
+        switch (nq) {
+            case 1: mma(std::integral_constant<int, 1>{}, buf); break;
+            case 2: mma(std::integral_constant<int, 2>{}, buf); break;
+            case 3: mma(std::integral_constant<int, 3>{}, buf); break;
+            case 4: mma(std::integral_constant<int, 4>{}, buf); break;
+            default: break;
+        }
+    };
     Stage R;
     load(0, R);
     store(0, 0, R);
     __syncthreads();
     for (int st = 0; st < nsteps; ++st) {
         if (st + 1 < nsteps) load(st + 1, R);
-        compute(st & 1);
+        compute(nbuf == 2 ? st & 1 : 0);
+        if (nbuf == 1) __syncthreads();
+        if (st + 1 < nsteps) store(st + 1, nbuf == 2 ? (st + 1) & 1 : 0, R);
+        __syncthreads();
+    }
+    double* G = a.part64 + (int64_t)(a.sub_base + s) * a.gsize + a.goff[m];
+#pragma unroll
+    for (int q = 0; q < TPW; ++q) {
+        if (q >= nq) continue;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            put_entry(G, K, nb, nl, ti[q], tj[q], ti[q] * TS + (lane >> 4) + 4 * r, tj[q] * TS + (lane & 15),
+                      acc[q][r]);
+    }
+}
+
+// FP32: 32x32x2 MFMA, eight wavefronts with up to two tiles each. The FP32
+// accumulators are emptied into FP64 registers after every kUnit primaries
+// (both parts), so single precision only ever sums a few dozen products.
+// An MFMA sums primaries k and k + 1, one per lane half, in the order of
+// k; a unit's row in LDS holds its even primaries, then its odd ones, so that
+// a lane reads four MFMAs' operands at once (row stride 36 floats: no bank
+// conflicts). With weights the columns stay bin-major and every tile is
+// formed: the weight multiplies the first column of a pair, and the rounding
+// of w x depends on which that is. PERF32
+constexpr int kF32Waves = 8, kF32TPW = 2, kF32Stride = kUnit + 4;
+
+__host__ __device__ constexpr size_t f32_lds(int flat_cols, int units, int nbuf) {
+    return (size_t)nbuf * ((size_t)flat_cols * kF32Stride + (size_t)units * kUnit) * sizeof(float);
+}
+
+template <bool W, int IPT>
+__global__ void __launch_bounds__(64 * kF32Waves) k_contract_f32(ContractArgs a, int cols) {
+    constexpr int TS = 32, TPW = kF32TPW, KSP = kF32Stride;
+    extern __shared__ unsigned char smem[];
+    const int s = blockIdx.x, m = blockIdx.y;
+    const int nb = a.nb, nl = a.lmax - m + 1, K = nb * nl;
+    const int ncol = (K + TS - 1) / TS * TS;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    int ti[TPW], tj[TPW], all;
+    const int t0 = blockIdx.z * kF32Waves * TPW;
+    const int nq = pick_tiles<TS>(K, nb, W ? a.lmax : a.lcouple, t0 + wave, kF32Waves, ti, tj, all);
+    if (t0 >= all) return;
+    const int parts = m == 0 ? 1 : 2;
+    const int units = step_units(ncol, cols);
+    const int64_t pa = a.sub_start[s], pb = a.sub_start[s + 1];
+    const int total = (int)((pb - pa + kUnit - 1) / kUnit) * parts;
+    const int nsteps = (total + units - 1) / units;
+    const Items<IPT, !W> it(threadIdx.x, 64 * kF32Waves, units, ncol, K, nb, n_values(a.lmax), value_offset(a.lmax, m));
+    const float* A = reinterpret_cast<const float*>(a.A);
+    float* lds = reinterpret_cast<float*>(smem);
+    const int bufsz = units * (ncol * KSP + kUnit);
+
+    struct Stage {
+        float4 x[IPT];
+        float w;
+    };
+    auto load = [&](int st, Stage& R) {
+#pragma unroll
+        for (int u = 0; u < IPT; ++u) {
+            const int g = st * units + max(it.unit[u], 0);
+            const int64_t p0 = pa + (int64_t)(g / parts) * kUnit;
+            const bool in = it.row[u] >= 0 && g < total;
+            const float* src =
+                A + (in ? (int64_t)(it.row[u] + (g % parts) * nl) * a.ldA + p0 + (p0 + it.k4 < pb ? it.k4 : 0) : 0);
+            __builtin_memcpy(&R.x[u], src, 16);
+        }
+        if constexpr (W) {
+            const int64_t p = pa + (int64_t)((st * units + (int)threadIdx.x / kUnit) / parts) * kUnit + threadIdx.x % kUnit;
+            R.w = a.pw[a.p_begin + (p < pb ? p : pa)];
+        }
+    };
+    // position of primary k inside a unit's row: the even ones first
+    auto store = [&](int st, int buf, const Stage& R) {
+        float* base = lds + buf * bufsz;
+        if constexpr (W) {
+            const int t = threadIdx.x, k = t % kUnit;
+            if (t < units * kUnit) base[units * ncol * KSP + (t - k) + (k & 1) * (kUnit / 2) + k / 2] = R.w;
+        }
+#pragma unroll
+        for (int u = 0; u < IPT; ++u) {
+            if (it.unit[u] < 0) continue;
+            const int g = st * units + it.unit[u];
+            const int kv = it.row[u] >= 0 && g < total
+                               ? (int)min((int64_t)kUnit, pb - pa - (int64_t)(g / parts) * kUnit) - it.k4 : 0;
+            const float2 ev = make_float2(kv > 0 ? R.x[u].x : 0.f, kv > 2 ? R.x[u].z : 0.f);
+            const float2 od = make_float2(kv > 1 ? R.x[u].y : 0.f, kv > 3 ? R.x[u].w : 0.f);
+            float* dst = base + (it.unit[u] * ncol + it.col[u]) * KSP + it.k4 / 2;
+            *reinterpret_cast<float2*>(dst) = ev;
+            *reinterpret_cast<float2*>(dst + kUnit / 2) = od;
+        }
+    };
+    f32x16 acc[TPW];
+    double accd[TPW][16];
+#pragma unroll
+    for (int q = 0; q < TPW; ++q) {
+        acc[q] = (f32x16)0.0f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) accd[q][r] = 0.0;
+    }
+    const int i = lane & 31, kg = lane >> 5;
+    auto mma = [&](auto nqc, int st, int buf) {
+        constexpr int NQ = decltype(nqc)::value;
+        const float* base = lds + buf * bufsz;
+        for (int u = 0; u < units; ++u) {
+            const float* X = base + u * ncol * KSP + kg * (kUnit / 2);
+            const float* wt = base + units * ncol * KSP + u * kUnit + kg * (kUnit / 2);
+#pragma unroll
+            for (int k = 0; k < kUnit / 2; k += 4) {
+                float4 wv = make_float4(1.f, 1.f, 1.f, 1.f);
+                if constexpr (W) wv = *reinterpret_cast<const float4*>(wt + k);
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+                    float4 av = *reinterpret_cast<const float4*>(X + (ti[q] * TS + i) * KSP + k);
+                    const float4 bv = *reinterpret_cast<const float4*>(X + (tj[q] * TS + i) * KSP + k);
+                    if constexpr (W) {
+                        av.x *= wv.x;
+                        av.y *= wv.y;
+                        av.z *= wv.z;
+                        av.w *= wv.w;
+                    }
+                    acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.x, bv.x, acc[q], 0, 0, 0);
+                    acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.y, bv.y, acc[q], 0, 0, 0);
+                    acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.z, bv.z, acc[q], 0, 0, 0);
+                    acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(av.w, bv.w, acc[q], 0, 0, 0);
+                }
+            }
+            if ((st * units + u) % parts == parts - 1) {
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) accd[q][r] += (double)acc[q][r];
+                    acc[q] = (f32x16)0.0f;
+                }
+            }
+        }
+    };
+    Stage R;
+    load(0, R);
+    store(0, 0, R);
+    __syncthreads();
+    for (int st = 0; st < nsteps; ++st) {
+        if (st + 1 < nsteps) load(st + 1, R);
+        if (nq == 2) mma(std::integral_constant<int, 2>{}, st, st & 1);
+        else if (nq == 1) mma(std::integral_constant<int, 1>{}, st, st & 1);
         if (st + 1 < nsteps) store(st + 1, (st + 1) & 1, R);
         __syncthreads();
     }
-    const int64_t sg = (int64_t)(a.sub_base + s);
+    double* G = a.part64 + (int64_t)(a.sub_base + s) * a.gsize + a.goff[m];
 #pragma unroll
     for (int q = 0; q < TPW; ++q) {
-        if (!tv[q]) continue;
-        const int j = lane & 15;
+        if (q >= nq) continue;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int ii = (lane >> 4) + 4 * r;
-            const int ci = ti[q] * TS + ii, cj = tj[q] * TS + j;
-            if (ci < K && cj < K) a.part64[sg * a.gsize + a.goff[m] + (int64_t)ci * K + cj] = acc64[q][r];
-        }
+        for (int r = 0; r < 16; ++r)
+            put_entry<!W>(G, K, nb, nl, ti[q], tj[q], ti[q] * TS + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3),
+                      tj[q] * TS + (lane & 31), accd[q][r]);
     }
 }
 
@@ -674,35 +668,9 @@ __global__ void __launch_bounds__(64 * kBfWaves) k_contract_bf16(ContractArgs a,
     uint16_t* lds = reinterpret_cast<uint16_t*>(smem);
     const float* A = reinterpret_cast<const float*>(a.A);
 
-    // Columns are l-major (column c holds l - m = c / nb of bin c % nb), so
-    // the l of a 32-column tile spans a few consecutive values. The tiles of
-    // the upper triangle whose columns couple some l1, l2 with |l1 - l2| <=
-    // lcouple are the needed ones; this wave takes the (t0 + wave + 8 q)-th
-    // of them in row-major order. (Along a row of tiles the smallest l
-    // distance only grows, so a row ends at its first tile past the limit.)
-    int ti[kBfTPW], tj[kBfTPW];
-    bool tv[kBfTPW];
-#pragma unroll
-    for (int q = 0; q < kBfTPW; ++q) {
-        ti[q] = tj[q] = 0;
-        tv[q] = false;
-    }
-    int nneed = 0;
-    for (int r = 0; r < nt; ++r) {
-        const int lhi = (min(K, r * TS + TS) - 1) / nb;
-        for (int c2 = r; c2 < nt; ++c2) {
-            if (c2 * TS / nb - lhi > a.lcouple) break;
-#pragma unroll
-            for (int q = 0; q < kBfTPW; ++q)
-                if (nneed == t0 + wave + kBfWaves * q) {
-                    ti[q] = r;
-                    tj[q] = c2;
-                    tv[q] = true;
-                }
-            ++nneed;
-        }
-    }
-    if (t0 >= nneed) return;
+    int ti[kBfTPW], tj[kBfTPW], all;
+    const int nq = pick_tiles<TS>(K, nb, a.lcouple, t0 + wave, kBfWaves, ti, tj, all);
+    if (t0 >= all) return;
     f32x16 acc32[kBfTPW];
     double accd[kBfTPW][16];
 #pragma unroll
@@ -838,13 +806,12 @@ __global__ void __launch_bounds__(64 * kBfWaves) k_contract_bf16(ContractArgs a,
             if (KS > 128) flush();
         }
     };
-    // MFMAs of step st from LDS buffer buf, then the FP64 flushes (a second
-    // tile of a wave is valid only if its first is)
+    // MFMAs of step st from LDS buffer buf, then the FP64 flushes
     auto compute = [&](int st, int buf) {
         const uint16_t* xp = lds + buf * bufsz;
         const uint16_t* wp = weighted ? xp + NPC * plane : xp;
-        if (tv[1]) mma(std::integral_constant<int, 2>{}, xp, wp);
-        else if (tv[0]) mma(std::integral_constant<int, 1>{}, xp, wp);
+        if (nq == 2) mma(std::integral_constant<int, 2>{}, xp, wp);
+        else if (nq == 1) mma(std::integral_constant<int, 1>{}, xp, wp);
         if (KS <= 128 && st % parts == parts - 1) flush();
     };
 
@@ -878,24 +845,14 @@ __global__ void __launch_bounds__(64 * kBfWaves) k_contract_bf16(ContractArgs a,
             __syncthreads();
         }
     }
-    // Each unordered column pair is written once (in a diagonal tile, the
-    // entry with the smaller l-major column first), at the upper-triangle
-    // position of the bin-major order c = b (lmax - m + 1) + l - m that the
-    // reduction, finalize and export read.
-    const int64_t sg = (int64_t)(a.sub_base + s);
+    double* G = a.part64 + (int64_t)(a.sub_base + s) * a.gsize + a.goff[m];
 #pragma unroll
     for (int q = 0; q < kBfTPW; ++q) {
-        if (!tv[q]) continue;
-        const int j = lane & 31;
+        if (q >= nq) continue;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int ii = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-            const int ci = ti[q] * TS + ii, cj = tj[q] * TS + j;
-            if (ci < K && cj < K && (ti[q] < tj[q] || ci <= cj)) {
-                const int oi = (ci % nb) * nl + ci / nb, oj = (cj % nb) * nl + cj / nb;
-                a.part64[sg * a.gsize + a.goff[m] + (int64_t)min(oi, oj) * K + max(oi, oj)] = accd[q][r];
-            }
-        }
+        for (int r = 0; r < 16; ++r)
+            put_entry(G, K, nb, nl, ti[q], tj[q], ti[q] * TS + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3),
+                      tj[q] * TS + (lane & 31), accd[q][r]);
     }
 }
 
@@ -911,7 +868,7 @@ constexpr int kSelfTasks = 16;
 constexpr int kSelfMaxSub = 4096;  // primaries per subchunk
 constexpr int kSelfUnroll = 16;
 
-template <bool UNIT>
+template <bool UNIT, typename T>
 __global__ void __launch_bounds__(256) k_self_moments(SelfArgs a) {
     __shared__ double wsh[UNIT ? 1 : kSelfMaxSub];
     const int s = blockIdx.x;
@@ -927,7 +884,7 @@ __global__ void __launch_bounds__(256) k_self_moments(SelfArgs a) {
         for (int i = threadIdx.x; i < n; i += 256) wsh[i] = a.pd[a.p_begin + pa + i].w;
         __syncthreads();
     }
-    const int nfull = n / (64 * kSelfUnroll) * (64 * kSelfUnroll);
+    constexpr int kSpan = 64 * kSelfUnroll;
     for (int q = 0; q < kSelfTasks / 4; ++q) {
         const int task = blockIdx.y * kSelfTasks + wave * (kSelfTasks / 4) + q;
         if (task >= ntask) break;
@@ -937,22 +894,29 @@ __global__ void __launch_bounds__(256) k_self_moments(SelfArgs a) {
         if (a.self_lo && L > a.lmax && L < nL) {
             // not written by the harmonic pass of such a run: the moment is zero
         } else if (L < nL) {
-            const int64_t row = ((int64_t)b * NV + na + L) * a.ldA + pa;
-            auto val = [&](int p) {
-                return a.fp64 ? reinterpret_cast<const double*>(a.A)[row + p]
-                              : (double)reinterpret_cast<const float*>(a.A)[row + p];
-            };
-            for (int p0 = 0; p0 < nfull; p0 += 64 * kSelfUnroll) {
-                double v[kSelfUnroll];
-#pragma unroll
-                for (int u = 0; u < kSelfUnroll; ++u) v[u] = val(p0 + 64 * u + lane);
+            const T* row = reinterpret_cast<const T*>(a.A) + ((int64_t)b * NV + na + L) * a.ldA + pa;
+            auto span = [&](int p0, auto whole) {
+                // the last span is masked, its loads clamped into the row, so
+                // that they are in flight together too. The values wait in the
+                // operand's own type (converted and chosen per load, they
+                // cost twice the registers and a branch: 2.33 ms against 0.73
+                // for 64 catalogues at lmax 10)
+                constexpr bool ALL = decltype(whole)::value;
+                T v[kSelfUnroll];
 #pragma unroll
                 for (int u = 0; u < kSelfUnroll; ++u) {
                     const int p = p0 + 64 * u + lane;
-                    acc[u & 3] += UNIT ? v[u] : wsh[p] * v[u];
+                    v[u] = row[ALL ? p : min(p, n - 1)];
                 }
-            }
-            for (int p = nfull + lane; p < n; p += 64) acc[0] += UNIT ? val(p) : wsh[p] * val(p);
+#pragma unroll
+                for (int u = 0; u < kSelfUnroll; ++u) {
+                    const int p = p0 + 64 * u + lane;
+                    if (ALL || p < n) acc[u & 3] += UNIT ? (double)v[u] : wsh[p] * (double)v[u];
+                }
+            };
+            int p0 = 0;
+            for (; p0 + kSpan <= n; p0 += kSpan) span(p0, std::true_type{});
+            if (p0 < n) span(p0, std::false_type{});
         } else {
             for (int p0 = 0; p0 < n; p0 += 256) {
 #pragma unroll
@@ -1125,44 +1089,57 @@ __global__ void k_export_alm(AlmExportArgs a) {
     a.out[2 * idx + 1] = im;
 }
 
-template <int MODE>
-size_t contract_lds(int ncol) {
-    using C = Cfg<MODE>;
-    constexpr int KSP = MODE >= 2 ? C::KS + 8 : C::KS + 1;
-    // bytes per staged element: value (fp64/fp32) or 2 x pieces x 2 bytes (BF16 planes of
-    // x and of w x)
-    size_t x = MODE == 0 ? sizeof(double) : (MODE == 1 ? sizeof(float) : (MODE == 2 ? 8 : 12));
-    return C::KS * sizeof(double) + (size_t)ncol * KSP * x;
+// Flat columns that a step of the FP64 / FP32 contraction stages: 128 / 256
+// (two / four items per thread: every m of up to 128 / 256 columns, the narrow
+// ones several units at a time), else all columns of the widest m, with as
+// many items per thread as they take.
+struct StepPlan { int ncol, cols, nbuf; size_t lds; };
+StepPlan step_plan(bool f64, int nb, int lmax) {
+    const int TS = f64 ? 16 : 32, base = f64 ? 128 : 256;
+    StepPlan p;
+    p.ncol = (nb * (lmax + 1) + TS - 1) / TS * TS;
+    p.cols = std::max(base, p.ncol);
+    // the largest step over the m: whole units within p.cols flat columns, at
+    // most 8 units (a unit of the widest m alone where it exceeds p.cols / 2)
+    p.nbuf = !f64 || f64_lds(p.cols, 8, 2) <= 160 * 1024 ? 2 : 1;
+    p.lds = f64 ? f64_lds(p.cols, 8, p.nbuf) : f32_lds(p.cols, 8, p.nbuf);
+    return p;
 }
 
-template <int MODE>
-hipError_t launch_contract_mode(const ContractArgs& a, hipStream_t s) {
-    using C = Cfg<MODE>;
-    const int K0 = a.nb * (a.lmax + 1);
-    const int nt0 = (K0 + C::TS - 1) / C::TS;
-    const int ntiles0 = nt0 * (nt0 + 1) / 2;
-    const int ngroups = (ntiles0 + 4 * C::TPW - 1) / (4 * C::TPW);
-    if constexpr (MODE == 0) {
-        // the double-buffered kernel when its items and buffers fit
-        const int ncol = nt0 * C::TS;
-        const size_t lds2 = f64db_lds(ncol);
-        if (ncol * (C::KS / 4) <= 256 * kF64IPT && lds2 <= 160 * 1024) {
-            const hipError_t e = a.unit_weights ? allow_full_lds((const void*)k_contract_f64<false>)
-                                                : allow_full_lds((const void*)k_contract_f64<true>);
-            if (e != hipSuccess) return e;
-            const dim3 grid(a.nsub, a.lmax + 1, ngroups);
-            if (a.unit_weights)
-                hipLaunchKernelGGL(k_contract_f64<false>, grid, dim3(256), lds2, s, a);
-            else
-                hipLaunchKernelGGL(k_contract_f64<true>, grid, dim3(256), lds2, s, a);
-            return hipGetLastError();
-        }
-    }
-    const size_t lds = contract_lds<MODE>(nt0 * C::TS);
-    const hipError_t e = allow_full_lds((const void*)k_contract<MODE>);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_contract<MODE>, dim3(a.nsub, a.lmax + 1, ngroups), dim3(256), lds, s, a);
-    return hipGetLastError();
+template <bool W>
+hipError_t launch_contract_f64(const ContractArgs& a, const StepPlan& p, hipStream_t s) {
+    const int nt = p.ncol / 16;
+    const dim3 grid(a.nsub, a.lmax + 1, (nt * (nt + 1) / 2 + kF64Waves * kF64TPW - 1) / (kF64Waves * kF64TPW));
+    auto run = [&](auto ipt) {
+        constexpr int IPT = decltype(ipt)::value;
+        const hipError_t e = allow_full_lds((const void*)k_contract_f64<W, IPT>);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_contract_f64<W, IPT>), grid, dim3(64 * kF64Waves), p.lds, s, a, p.cols, p.nbuf);
+        return hipGetLastError();
+    };
+    if (p.cols <= 128) return run(std::integral_constant<int, 2>{});
+    if (p.cols <= 256) return run(std::integral_constant<int, 4>{});
+    return run(std::integral_constant<int, 9>{});
+}
+
+template <bool W>
+hipError_t launch_contract_f32(const ContractArgs& a, const StepPlan& p, hipStream_t s) {
+    const int nt = p.ncol / 32;
+    const dim3 grid(a.nsub, a.lmax + 1, (nt * (nt + 1) / 2 + kF32Waves * kF32TPW - 1) / (kF32Waves * kF32TPW));
+    auto run = [&](auto ipt) {
+        constexpr int IPT = decltype(ipt)::value;
+        const hipError_t e = allow_full_lds((const void*)k_contract_f32<W, IPT>);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_contract_f32<W, IPT>), grid, dim3(64 * kF32Waves), p.lds, s, a, p.cols);
+        return hipGetLastError();
+    };
+    return p.cols <= 256 ? run(std::integral_constant<int, 4>{}) : run(std::integral_constant<int, 9>{});
+}
+
+hipError_t launch_contract_plain(const ContractArgs& a, bool f64, hipStream_t s) {
+    const StepPlan p = step_plan(f64, a.nb, a.lmax);
+    if (f64) return a.unit_weights ? launch_contract_f64<false>(a, p, s) : launch_contract_f64<true>(a, p, s);
+    return a.unit_weights ? launch_contract_f32<false>(a, p, s) : launch_contract_f32<true>(a, p, s);
 }
 
 }  // namespace
@@ -1236,15 +1213,15 @@ hipError_t launch_contract_iso(const ContractArgs& a, hipStream_t s) {
 hipError_t launch_contract(const ContractArgs& a, hipStream_t s) {
     if (a.nsub <= 0) return hipSuccess;
     switch (a.mode) {
-        case 0: return launch_contract_mode<0>(a, s);
-        case 1: return launch_contract_mode<1>(a, s);
+        case 0: return launch_contract_plain(a, true, s);
+        case 1: return launch_contract_plain(a, false, s);
         case 2:
         case 3: {
             // a split-BF16 step must stage at least 16 primaries of every
             // column in the threads' registers (nbins (lmax + 1) <= 512 with
             // weights); beyond that the FP32 MFMA contraction runs instead
             if (bf_plan(a.mode == 2 ? 2 : 3, a.nb, a.lmax, !a.unit_weights, a.ks_max).nbuf == 0)
-                return launch_contract_mode<1>(a, s);
+                return launch_contract_plain(a, false, s);
             return a.mode == 2 ? launch_contract_bf16<2>(a, s) : launch_contract_bf16<3>(a, s);
         }
         default: return hipErrorInvalidValue;
@@ -1252,25 +1229,18 @@ hipError_t launch_contract(const ContractArgs& a, hipStream_t s) {
 }
 
 size_t contract_lds_bytes(int mode, int nb, int lmax) {
-    const int K0 = nb * (lmax + 1);
-    switch (mode) {
-        case 0: return contract_lds<0>((K0 + 15) / 16 * 16);
-        case 1: return contract_lds<1>((K0 + 31) / 32 * 32);
-        default: {
-            const BfPlan pl = bf_plan(mode == 2 ? 2 : 3, nb, lmax, true);
-            return pl.nbuf ? pl.lds : contract_lds<1>((K0 + 31) / 32 * 32);
-        }
-    }
+    if (mode <= 1) return step_plan(mode == 0, nb, lmax).lds;
+    const BfPlan pl = bf_plan(mode == 2 ? 2 : 3, nb, lmax, true);
+    return pl.nbuf ? pl.lds : step_plan(false, nb, lmax).lds;
 }
 
 hipError_t launch_self_moments(const SelfArgs& a, hipStream_t s) {
     if (a.nsub <= 0) return hipSuccess;
     const int ntask = a.nb * (2 * a.lmax + 2);
     const dim3 grid(a.nsub, (ntask + kSelfTasks - 1) / kSelfTasks);
-    if (a.unit_w)
-        hipLaunchKernelGGL(k_self_moments<true>, grid, dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL(k_self_moments<false>, grid, dim3(256), 0, s, a);
+    auto run = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, a); };
+    if (a.unit_w) a.fp64 ? run(k_self_moments<true, double>) : run(k_self_moments<true, float>);
+    else a.fp64 ? run(k_self_moments<false, double>) : run(k_self_moments<false, float>);
     return hipGetLastError();
 }
 

@@ -93,3 +93,63 @@ def test_edge_correction_pivoting(torch, lmax, nb):
     off = np.abs(got - ref).max(axes)
     say(f"  largest error over tolerance {float((off / tol).max()):.2e}")
     assert np.all(off <= tol)
+
+
+# (points, bins, lmax): the subchunk of a catalogue changes at 256 points, and
+# from 256 to 512 primaries at 16,384 (FP64, FP32) points; K = nbins (lmax + 1)
+# columns: one tile, 128 and 144 (the FP64 step's columns per thread change),
+# 256 and 272 (the FP32 ones; one FP64 buffer), 544 (the largest operand)
+@pytest.mark.parametrize("n,nb,lmax", [(3, 1, 0), (255, 5, 2), (257, 7, 4), (16384, 2, 1), (16385, 2, 1), (300, 8, 15),
+                                       (290, 9, 15), (270, 16, 15), (270, 17, 15), (260, 32, 16)])
+@pytest.mark.parametrize("prec,weighted", [(T.PREC_FP64, False), (T.PREC_FP64, True), (T.PREC_FP32, False),
+                                           (T.PREC_FP32, True), (T.PREC_MIXED_BF16X6, False)])
+def test_contraction_of_exported_alm(torch, n, nb, lmax, prec, weighted):
+    """NNN^m with degenerate triangles kept against the same sums of the
+    handle's own a_lm in double precision. Tolerance relative to the norms of
+    the two columns: FP64 sums of n terms, n 2^-53 and the export's few
+    roundings; FP32 and six-product sums of at most 256 products before they
+    go to FP64, (256 + 8) 2^-24."""
+    box = 100.0 if n < 1000 else 300.0
+    edges = np.linspace(1.0, 45.0, nb + 1) if n < 1000 else np.linspace(1.0, 20.0, nb + 1)
+    pos = C.poisson(n, box, 40 + n)
+    w = np.random.default_rng(n).uniform(-1.0, 1.0, n) if weighted else None
+    say(f"  contraction: n={n} nb={nb} lmax={lmax} prec={prec} weighted={weighted}")
+    h = T.Handle(box, edges, lmax, precision=prec, flags=T.F_KEEP_DEGENERATE)
+    h.build_grid(torch.from_numpy(pos).cuda(), None if w is None else torch.from_numpy(w).cuda(), n)
+    h.alm_accumulate()
+    a = h.get_alm(0, n).cpu()
+    nnn = h.contract(export=True).cpu().numpy()
+    h.close()
+    wt = torch.ones(n, dtype=torch.float64) if w is None else torch.from_numpy(w.astype(np.float32).astype(np.float64)
+                                                                          if prec != T.PREC_FP64 else w)
+    tol = (n + 32) * 2.0 ** -53 if prec == T.PREC_FP64 else 264 * 2.0 ** -24
+    for m in range(lmax + 1):
+        x = a[:, :, m:, m].reshape(n, -1)  # (b, l) columns
+        re, im = x.real.contiguous(), x.imag.contiguous()
+        ref = (re * wt[:, None]).T @ re + (im * wt[:, None]).T @ im
+        norm = torch.sqrt(((re * re + im * im) * wt.abs()[:, None]).sum(0))
+        k = lmax + 1 - m
+        got = torch.from_numpy(nnn[m, m:, m:]).permute(2, 0, 3, 1).reshape(nb * k, nb * k)
+        off = (got - ref).abs() - tol * norm[:, None] * norm[None, :]
+        assert float(off.max()) <= 0.0, (m, float(off.max()))
+
+
+@pytest.mark.parametrize("prec", [T.PREC_FP64, T.PREC_FP32])
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("nb,lmax,Lmax", [(10, 10, 0), (10, 10, 2), (3, 12, 4), (32, 6, 2)])
+def test_plain_coupled_tiles_batched_equals_steps(torch, prec, weighted, nb, lmax, Lmax):
+    """A batched run forms only the tiles its multipoles couple; the step
+    calls form all: the same multipoles, bit for bit."""
+    n, box, edges = 300, 100.0, np.linspace(2.0, 40.0, nb + 1)
+    pos = torch.from_numpy(C.poisson(n, box, 91)).cuda()
+    w = torch.from_numpy(np.random.default_rng(3).uniform(-1.0, 1.0, n)).cuda() if weighted else None
+    mults = O.all_multipoles(lmax, Lmax)
+    say(f"  coupled tiles: nb={nb} lmax={lmax} Lmax={Lmax} prec={prec} weighted={weighted}")
+    h = T.Handle(box, edges, lmax, precision=prec)
+    batched = h.run_catalogs([n], [n], pos, w, mults)[0].cpu().numpy()
+    h.build_grid(pos, w, n)
+    h.alm_accumulate()
+    h.contract()
+    steps = h.multipoles(mults).cpu().numpy()
+    h.close()
+    assert np.array_equal(batched, steps)
