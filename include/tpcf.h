@@ -408,7 +408,7 @@ tpcf_status tpcf_covariance_noalloc(tpcf_handle h, int32_t n_mocks, int64_t stri
 /*
  * Precision matrix with the Hartlap correction (eq. (Hartlap)):
  *   d_prec = (N_m - N_d - 2)/(N_m - 1) * inverse(d_cov),
- * by a Gauss-Jordan sweep in FP64 (d_prec may equal d_cov: in place).
+ * by block Gauss-Jordan in FP64 (d_prec may equal d_cov: in place).
  * n_d in 1 .. 4096 and n_mocks >= n_d + 3 (else TPCF_ERR_RANGE); a matrix that
  * is not positive definite gives TPCF_ERR_RANGE. Synchronises the stream.
  */

@@ -1627,11 +1627,9 @@ tpcf_status tpcf_precision_matrix(tpcf_handle h, int32_t n_d, const double* d_co
     tpcf_status st;
     if ((st = ensure(h, h->d_covflag, sizeof(int))) != TPCF_OK) return st;
     HIPCHK(launch_fill_i32(P<int>(h->d_covflag), 1, 0, h->stream));
-    if (d_prec != d_cov)
-        HIPCHK(hipMemcpyAsync(d_prec, d_cov, sizeof(double) * (size_t)n_d * n_d, hipMemcpyDeviceToDevice, h->stream));
     const double hartlap = (n_mocks - n_d - 2.0) / (n_mocks - 1.0);
     if ((st = ensure(h, h->d_covpart, sizeof(double) * (size_t)n_d * n_d)) != TPCF_OK) return st;
-    HIPCHK(launch_cov_invert(d_prec, P<double>(h->d_covpart), n_d, hartlap, P<int>(h->d_covflag), h->stream));
+    HIPCHK(launch_cov_invert(d_cov, d_prec, P<double>(h->d_covpart), n_d, hartlap, P<int>(h->d_covflag), h->stream));
     int bad = 0;
     HIPCHK(hipMemcpyAsync(&bad, h->d_covflag.p, sizeof(int), hipMemcpyDeviceToHost, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));

@@ -211,9 +211,9 @@ hipError_t launch_cov(const double* src, int64_t stride, const int64_t* off, int
 constexpr int64_t kCovScratchBytes = 32ll << 20;
 hipError_t cov_scratch_init(int device, void** out);
 int64_t cov_scratch_need(int nm, int nd);
-// A (n x n, symmetric positive definite) <- scale * A^-1 in place, W (n x n) as workspace;
+// A <- scale * C^-1 (n x n, C symmetric positive definite; C may be A), W (n x n) as workspace;
 // *bad |= 1 on a non-positive pivot.
-hipError_t launch_cov_invert(double* A, double* W, int n, double scale, int* bad, hipStream_t s);
+hipError_t launch_cov_invert(const double* C, double* A, double* W, int n, double scale, int* bad, hipStream_t s);
 
 // Contraction (tpcf_contract.hip)
 struct ContractArgs {

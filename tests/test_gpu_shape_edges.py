@@ -153,3 +153,55 @@ def test_plain_coupled_tiles_batched_equals_steps(torch, prec, weighted, nb, lma
     steps = h.multipoles(mults).cpu().numpy()
     h.close()
     assert np.array_equal(batched, steps)
+
+
+# 32 x 32 pivot blocks: below, at and above one, two and three of them
+@pytest.mark.parametrize("nd", [1, 2, 31, 32, 33, 64, 65, 96, 97, 333])
+def test_precision_block_edges(torch, nd):
+    """Block Gauss-Jordan at the edges of its blocks, out of place and in
+    place (an odd number of blocks takes a copy), against numpy; the tolerance
+    is 32 n eps cond. A matrix whose last pivot is negative is refused."""
+    rng = np.random.default_rng(nd)
+    L = np.tril(rng.uniform(-0.3, 1.0, (nd, nd))) + 2.0 * np.eye(nd)
+    c, nm = L @ L.T, nd + 50
+    h = T.Handle(100.0, np.linspace(0.0, 10.0, 2), 0)
+    cov = torch.from_numpy(c).cuda()
+    got = h.precision(cov, nm).cpu().numpy()
+    assert np.array_equal(cov.cpu().numpy(), c)
+    h.precision(cov, nm, out=cov)
+    assert np.array_equal(cov.cpu().numpy(), got)
+    ref = np.linalg.inv(c) * (nm - nd - 2.0) / (nm - 1.0)
+    tol = 32.0 * nd * 2.0 ** -53 * np.linalg.cond(c) * np.abs(ref).max()
+    say(f"  precision nd={nd}: error over tolerance {np.abs(got - ref).max() / tol:.2e}")
+    assert np.abs(got - ref).max() <= tol
+    c[-1, -1] -= 2.0 / np.linalg.inv(c)[-1, -1]  # the last Schur complement changes sign
+    with pytest.raises(T.TpcfError) as e:
+        h.precision(torch.from_numpy(c).cuda(), nm)
+    assert e.value.status == T.TPCF_ERR_RANGE
+    h.close()
+
+
+# chunks of 64 mocks, 64-entry columns, steps of 32 mocks in a slice
+@pytest.mark.parametrize("nm,nd", [(2, 1), (63, 15), (64, 16), (65, 17), (129, 64), (500, 65)])
+def test_covariance_chunk_edges(torch, nm, nd):
+    """Offsets with one outside the row (allocation-free entry): NaN in its row
+    and column alone, the rest as without it."""
+    rng = np.random.default_rng(nm)
+    src = rng.standard_normal((nm, nd + 3))
+    off = np.sort(rng.choice(nd + 3, nd, replace=False)).astype(np.int64)
+    h = T.Handle(100.0, np.linspace(0.0, 10.0, 2), 0)
+    S = torch.from_numpy(src).cuda()
+    mean, cov = h.covariance(S, offsets=off)
+    x = src[:, off]
+    ref = np.cov(x, rowvar=False).reshape(nd, nd)
+    # sums of nm products each within (nm + 4) 2^-53 of their magnitudes
+    sd = np.sqrt((x ** 2).sum(0))
+    assert np.all(np.abs(cov.cpu().numpy() - ref) <= 4.0 * (nm + 4) * 2.0 ** -53 * np.outer(sd, sd) / (nm - 1))
+    assert np.all(np.abs(mean.cpu().numpy() - x.mean(0)) <= (nm + 4) * 2.0 ** -53 * np.abs(x).max(0))
+    bad = torch.from_numpy(off).cuda()
+    bad[nd // 2] = nd + 3
+    mean2, cov2 = h.covariance_noalloc(S, offsets=bad)
+    keep = np.arange(nd) != nd // 2
+    assert np.isnan(mean2.cpu().numpy()[~keep]).all() and np.isnan(cov2.cpu().numpy()[~keep]).all()
+    assert np.array_equal(cov2.cpu().numpy()[keep][:, keep], cov.cpu().numpy()[keep][:, keep])
+    h.close()
