@@ -205,3 +205,28 @@ def test_covariance_chunk_edges(torch, nm, nd):
     assert np.isnan(mean2.cpu().numpy()[~keep]).all() and np.isnan(cov2.cpu().numpy()[~keep]).all()
     assert np.array_equal(cov2.cpu().numpy()[keep][:, keep], cov.cpu().numpy()[keep][:, keep])
     h.close()
+
+
+# one-cell grids whose candidates fill a staged load of 256, or one short of
+# it, or one over, and grids of cells; counts of points that leave 0, 1 and 63
+# candidates for the next tile
+@pytest.mark.parametrize("n", [2, 63, 64, 65, 255, 256, 257, 319, 320, 321, 513, 1025])
+@pytest.mark.parametrize("box,rmax,nmu", [(100.0, 50.0, 7), (400.0, 90.0, 200)])
+def test_xi_tile_edges(torch, n, box, rmax, nmu):
+    """Pair counts of clumped points (several tiles around the clump) with
+    coincident points, points closer than FP32 resolves and points whose FP32
+    separation is denormal: every count as the oracle's."""
+    pos = C.poisson(n, box, 300 + n)
+    half = n // 2
+    pos[:half] = np.mod(0.5 * box + 0.02 * (pos[:half] - 0.5 * box), box)
+    if n >= 63:
+        pos[1] = pos[0]
+        pos[3] = pos[2] + [1e-9, -1e-9, 2e-9]
+        pos[-1], pos[-2] = [1e-25, 0.0, 0.0], [3e-25, 0.0, 1e-25]
+    edges = np.linspace(0.0, rmax, 6) if n % 2 else np.array([0.0, 1e-24, 0.3, 0.5, 0.9, 1.0]) * rmax
+    say(f"  xi: n={n} box={box} nmu={nmu}")
+    h = T.Handle(box, edges, 0)
+    h.build_grid(torch.from_numpy(pos).cuda(), None, max(3, n))
+    dd = h.xi_count(nmu).cpu().numpy()
+    h.close()
+    assert np.array_equal(dd, O.xi_counts(pos, box, edges, nmu))
