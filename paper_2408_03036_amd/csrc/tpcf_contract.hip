@@ -961,18 +961,19 @@ __global__ void k_finalize(FinalArgs a) {
     const int nL = 2 * a.lmax + 1;
     const int sw = nb * (nL + 1);
     const double* G = a.G + (int64_t)c * a.gsize;
+    // of the self moments only the order L of the multipole has a coefficient
+    const int L = a.mult[3 * t + 2];
+    const bool self = b1 == b2 && a.subtract_self;
+    const double S = self ? a.S[(int64_t)c * sw + b1 * (nL + 1) + L] : 0.0;
     double sum = 0.0;
+#pragma unroll 4
     for (int m = 0; m <= mm; ++m) {
         const int nl = a.lmax - m + 1;
         const int K = nb * nl;
         const int ci = b1 * nl + (l1 - m), cj = b2 * nl + (l2 - m);
         const double g = G[a.goff[m] + (int64_t)min(ci, cj) * K + max(ci, cj)];
         sum += a.coefG[t * (a.lmax + 1) + m] * g;
-        if (b1 == b2 && a.subtract_self) {
-            const double* cs = a.coefS + ((int64_t)t * (a.lmax + 1) + m) * nL;
-            const double* S = a.S + (int64_t)c * sw + b1 * (nL + 1);
-            for (int L = 0; L < nL; ++L) sum -= cs[L] * S[L];
-        }
+        if (self) sum -= a.coefS[((int64_t)t * (a.lmax + 1) + m) * nL + L] * S;
     }
     const double nd = a.nd[c];
     const double rrr = nd * (nd - 1.0) * (nd - 2.0) * a.vol[b1] * a.vol[b2] * a.inv_box6;
