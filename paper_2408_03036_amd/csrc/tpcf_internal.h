@@ -110,7 +110,8 @@ struct BinArgs {
     int npmax;               // capacity of the piece table (>= 2 nruns)
     int uniform;             // bins equally spaced in r: bin = floor((r - e0) / dr)
     float e0f, inv_dr;       // FP32 first edge and 1 / bin width (uniform bins)
-    float delta;             // guard band in units of the bin width (uniform bins)
+    float delta;             // guard band in units of the bin width (uniform bins): binned after the tile
+    float delta_in;          // narrower band: decided in FP64
     float inv_boxf;          // 1 / L (single-cell mode)
     const int* item_start;   // [ncat*ncell+1] first work item of each cell
     const int* item_cell;    // [items] cell of each work item

@@ -260,8 +260,9 @@ __device__ __forceinline__ void put_hit(const BinArgs& a, const ItemCtx& c, int 
 // stores complete in order, so it also drains the tile's hit stores).
 //
 // A pair inside the guard band of an edge is only marked during the tests
-// (one bit per (tile slot, primary) of the lane) and binned exactly after
-// them, outside the test loop.
+// (one bit per (tile slot, primary) of the lane) and binned after them,
+// outside the test loop: exactly in FP64 if it is in the narrow part of the
+// band, which covers the FP32 error, else by the test's own value.
 template <int SWEEP, bool SINGLE, bool UNIFORM, int REC>
 __device__ __forceinline__ void bin_sweep(const BinArgs& a, const ItemCtx& c, const float (&px)[kGM],
                                           const float (&py)[kGM], const float (&pz)[kGM],
@@ -347,7 +348,7 @@ __device__ __forceinline__ void bin_sweep(const BinArgs& a, const ItemCtx& c, co
                                          c.tent + (buf ^ 1) * kTile + threadIdx.x + 64 * kNW * s, c.cst, c.cshift,
                                          a.g.hf, a.pw != nullptr);
         }
-        // the marked near-edge pairs, binned exactly (rare)
+        // the marked near-edge pairs (rare)
         if (__ballot(nearbits != 0) != 0ull) {
 #pragma unroll
             for (int g = 0; g < kGM; ++g) {
@@ -361,8 +362,20 @@ __device__ __forceinline__ void bin_sweep(const BinArgs& a, const ItemCtx& c, co
                     const uint32_t entry = cure[i];
                     float dx, dy, dz;
                     separation<SINGLE>(a, q, px[g], py[g], pz[g], dx, dy, dz);
-                    const int b = exact_pair<SINGLE>(a.pd, c.cs + c.wave + kNW * g, c.cstart, entry, c.mask,
-                                                     c.cshift, c.cx, c.cy, c.cz, a.g.k, a.g.nc, a.g.box, a.nb, T.e2);
+                    int b;
+                    bool sure = false;
+                    if constexpr (UNIFORM) {
+                        // the test's own u again: outside the narrow band its
+                        // bin is certain, and nothing is gathered
+                        const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+                        const float uu = fmaf(__builtin_amdgcn_sqrtf(r2), a.inv_dr, ne0);
+                        const float fl = floorf(uu), fr = uu - fl;
+                        sure = fr > a.delta_in && fr < 1.0f - a.delta_in;
+                        b = (unsigned)(int)fl < nbu ? (int)fl : -1;
+                    }
+                    if (!sure)
+                        b = exact_pair<SINGLE>(a.pd, c.cs + c.wave + kNW * g, c.cstart, entry, c.mask, c.cshift, c.cx,
+                                               c.cy, c.cz, a.g.k, a.g.nc, a.g.box, a.nb, T.e2);
                     put_hit<SWEEP, REC>(a, c, g, b >= 0, b, base[g], dx, dy, dz, q.w, entry);
                 }
             }

@@ -230,3 +230,31 @@ def test_xi_tile_edges(torch, n, box, rmax, nmu):
     dd = h.xi_count(nmu).cpu().numpy()
     h.close()
     assert np.array_equal(dd, O.xi_counts(pos, box, edges, nmu))
+
+
+# cells of r_max / k, and one cell (box = 2 r_max)
+@pytest.mark.parametrize("box,refine", [(400.0, 1), (400.0, 3), (400.0, 4), (120.0, 0)])
+@pytest.mark.parametrize("prec,weighted", [(T.PREC_FP64, False), (T.PREC_FP32, False), (T.PREC_FP32, True)])
+def test_separations_around_edges(torch, box, refine, prec, weighted):
+    """Half of the points lie at a bin edge from another one, off by 1e-9 to
+    1e-3 of it on either side: inside both guard bands, inside the wide one
+    only, and outside. The integer pair and triplet counts are the oracle's."""
+    rng = np.random.default_rng(17)
+    n, edges = 1500, np.linspace(10.0, 60.0, 6)
+    p = rng.uniform(0.0, box, (n, 3))
+    d = rng.standard_normal((n, 3))
+    d /= np.linalg.norm(d, axis=1, keepdims=True)
+    off = 10.0 ** rng.uniform(-9.0, -3.0, n) * rng.choice([-1.0, 1.0], n)
+    pos = np.vstack([p, np.mod(p + d * (rng.choice(edges, n) * (1.0 + off))[:, None], box)])
+    w = np.ones(2 * n) if weighted else None
+    say(f"  edges: box={box} refine={refine} prec={prec} weighted={weighted}")
+    h = T.Handle(box, edges, 0, precision=prec, grid_refine=refine)
+    h.build_grid(torch.from_numpy(pos).cuda(), None if w is None else torch.from_numpy(w).cuda(), 2 * n)
+    h.alm_accumulate()
+    h.contract()
+    got = h.multipoles([(0, 0, 0)]).cpu().numpy()
+    pairs = h.pair_count()
+    h.close()
+    ref, _, res = O.run(pos, box, edges, 0, [(0, 0, 0)])
+    assert pairs == res.npairs
+    assert np.abs(got - ref).max() <= 1e-12 * np.abs(ref).max()
