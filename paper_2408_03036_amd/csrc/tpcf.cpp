@@ -1478,7 +1478,13 @@ tpcf_status tpcf_xi_count(tpcf_handle h, int32_t nmu, int64_t* d_counts) {
     a.uniform = h->uniform;
     a.e0f = (float)h->edges[0];
     a.inv_dr = h->inv_dr;
-    a.delta = h->delta_in;
+    // What lies within the guard band beyond the outer edges has to come out
+    // as near an edge, for its bin is outside the histogram: the band of the
+    // near test is the wider one, by more than the two tests round differently
+    // (u - nb / 2 and nb / 2 + delta by half an ulp of nb each, the fraction
+    // and 0.5 - delta by 2^-25 each).
+    a.reach_u = 0.5f * (float)h->nb + h->delta_in;
+    a.delta = h->delta_in + 2.0f * (float)ulp32((double)h->nb + 1.0);
     a.inv_boxf = (float)(1.0 / h->cfg.box);
     a.reach2 = (float)(h->edges[h->nb] * h->edges[h->nb] * (1.0 + 2e-4));
     a.nmu = nmu;

@@ -173,6 +173,7 @@ struct XiArgs {
     const float* guard;      // [nb+1] FP32 guard band around each squared edge
     int uniform;             // bins equally spaced in r
     float e0f, inv_dr, delta;// uniform bins: first edge, 1 / width, guard band in bin units
+    float reach_u;           // uniform bins: largest |u - nb / 2| that is tested further
     float inv_boxf;          // 1 / L (single-cell mode)
     float reach2;            // squared reach of a work item's candidate cut (outer edge, with a margin)
     int nmu;                 // mu bins over [-1, 1]

@@ -232,6 +232,29 @@ def test_xi_tile_edges(torch, n, box, rmax, nmu):
     assert np.array_equal(dd, O.xi_counts(pos, box, edges, nmu))
 
 
+# shells ending at the top of a binade, in one and past it
+@pytest.mark.parametrize("box,rmin,rmax,nb", [(500.0, 0.0, 100.0, 20), (500.0, 10.0, 60.0, 5), (1000.0, 0.0, 150.0, 30),
+                                              (300.0, 0.0, 150.0, 8), (400.0, 20.0, 100.0, 1)])
+def test_xi_just_outside_the_shells(torch, box, rmin, rmax, nb):
+    """Pairs beyond the outer edge by steps finer than FP32 resolves, across
+    the guard band and on to 1e-3 of the radius: none is counted, and nothing
+    else is disturbed."""
+    rng = np.random.default_rng(23)
+    n, nmu = 6000, 24
+    p = rng.uniform(0.0, box, (n, 3))
+    d = rng.standard_normal((n, 3))
+    d /= np.linalg.norm(d, axis=1, keepdims=True)
+    off = np.concatenate([np.linspace(0.0, 3e-5, n - 500), np.geomspace(3e-5, 1e-3, 500)])
+    pos = np.vstack([p, np.mod(p + d * (rmax * (1.0 + off))[:, None], box)])
+    edges = np.linspace(rmin, rmax, nb + 1)
+    say(f"  xi outside: box={box} edges={rmin}..{rmax} nb={nb}")
+    h = T.Handle(box, edges, 0)
+    h.build_grid(torch.from_numpy(pos).cuda(), None, 2 * n)
+    dd = h.xi_count(nmu).cpu().numpy()
+    h.close()
+    assert np.array_equal(dd, O.xi_counts(pos, box, edges, nmu))
+
+
 # cells of r_max / k, and one cell (box = 2 r_max)
 @pytest.mark.parametrize("box,refine", [(400.0, 1), (400.0, 3), (400.0, 4), (120.0, 0)])
 @pytest.mark.parametrize("prec,weighted", [(T.PREC_FP64, False), (T.PREC_FP32, False), (T.PREC_FP32, True)])
