@@ -104,8 +104,8 @@ typedef struct {
                                 edges[nbins] <= box/2 (minimum image); copied at create       */
     int32_t lmax;            /* 0 .. 16. The harmonic pass keeps the a_lm of a (primary,
                                 bin) list in one lane's registers; above lmax 10 (FP32) or
-                                6 (FP64) it splits the m range over 2 launches, and from 13
-                                over 3 (FP32) or 4 (FP64), each rereading the lists. With
+                                6 (FP64) two wavefronts share the m range of 64 lists,
+                                three (FP32) from 15 and four (FP64) from 13. With
                                 weights and nbins (lmax + 1) > 512 the split-BF16
                                 precisions contract on FP32 MFMA.                          */
     int32_t precision;       /* tpcf_precision                                                */

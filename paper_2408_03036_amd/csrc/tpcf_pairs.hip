@@ -682,11 +682,19 @@ struct ChebTable {
     }
 };
 
-// Split point of the m range when the values of one bin do not fit one lane.
-__host__ __device__ constexpr int m_split(int lmax) {
+// Self moments a lane accumulates besides the a_lm: all 2 lmax + 1 orders,
+// those up to lmax (slo), and with unit weights only the orders above lmax
+// (the others equal the m = 0 sums).
+__host__ __device__ constexpr int self_live(int lmax, bool unit, bool slo) {
+    return unit ? (slo ? 0 : lmax) : (slo ? lmax + 1 : 2 * lmax + 1);
+}
+
+// Split point of the m range when the values of one bin do not fit one lane
+// (ns self moments are accumulated with m = 0).
+__host__ __device__ constexpr int m_split(int lmax, int ns) {
     // largest M such that values(m <= M) + self stay within half of all values
-    const int total = n_values(lmax);
-    int acc = 2 * lmax + 1 + (lmax + 1);
+    const int total = n_alm_values(lmax) + ns;
+    int acc = ns + (lmax + 1);
     int M = 0;
     while (M < lmax && 2 * (acc + 2 * (lmax - M)) <= total) {
         ++M;
@@ -699,12 +707,12 @@ __host__ __device__ constexpr int m_split(int lmax) {
 // moments with part 0, chosen to minimise the largest part's values. Returns
 // the first m of part p (p = np gives lmax + 1).
 __host__ __device__ constexpr int values_of_m(int lmax, int m) { return m == 0 ? lmax + 1 : 2 * (lmax - m + 1); }
-__host__ __device__ constexpr int part_first_m(int lmax, int np, int p) {
+__host__ __device__ constexpr int part_first_m(int lmax, int np, int p, int ns) {
     if (p <= 0) return 0;
     if (p >= np) return lmax + 1;
     // cumulative values before m = M (the self moments count with m = 0)
     int cum[64] = {};
-    cum[0] = 2 * lmax + 1;
+    cum[0] = ns;
     for (int m = 0; m <= lmax; ++m) cum[m + 1] = cum[m] + values_of_m(lmax, m);
     int best = 1 << 30, b1 = 1, b2 = 2, b3 = 3;
     for (int x1 = 1; x1 <= lmax; ++x1)
@@ -730,17 +738,20 @@ __host__ __device__ constexpr int part_first_m(int lmax, int np, int p) {
 // m_split; G = 3 .. 5 three parts; G = 6 .. 9 four parts.
 __host__ __device__ constexpr int part_np(int G) { return G == 0 ? 1 : (G <= 2 ? 2 : (G <= 5 ? 3 : 4)); }
 __host__ __device__ constexpr int part_ix(int G) { return G == 0 ? 0 : (G <= 2 ? G - 1 : (G <= 5 ? G - 3 : G - 6)); }
-__host__ __device__ constexpr int part_mlo(int lmax, int G) {
-    return G <= 2 ? (G == 2 ? m_split(lmax) + 1 : 0) : part_first_m(lmax, part_np(G), part_ix(G));
+__host__ __device__ constexpr int part_mlo(int lmax, int G, int ns) {
+    return G <= 2 ? (G == 2 ? m_split(lmax, ns) + 1 : 0) : part_first_m(lmax, part_np(G), part_ix(G), ns);
 }
-__host__ __device__ constexpr int part_mhi(int lmax, int G) {
-    return G <= 2 ? (G == 1 ? m_split(lmax) : lmax) : part_first_m(lmax, part_np(G), part_ix(G) + 1) - 1;
+__host__ __device__ constexpr int part_mhi(int lmax, int G, int ns) {
+    return G <= 2 ? (G == 1 ? m_split(lmax, ns) : lmax) : part_first_m(lmax, part_np(G), part_ix(G) + 1, ns) - 1;
 }
 
-template <typename T, int LMAX, int G>
+template <typename T_, int LMAX_, int G, bool UNIT, bool SLO>
 struct Acc {
-    static constexpr int MLO = part_mlo(LMAX, G);
-    static constexpr int MHI = part_mhi(LMAX, G);
+    using T = T_;
+    static constexpr int LMAX = LMAX_;
+    static constexpr int LIVE = self_live(LMAX, UNIT, SLO);
+    static constexpr int MLO = part_mlo(LMAX, G, LIVE);
+    static constexpr int MHI = part_mhi(LMAX, G, LIVE);
     static constexpr bool SELF = MLO == 0;
     static constexpr int V0 = value_offset(LMAX, MLO);
     static constexpr int V1 = value_offset(LMAX, MHI + 1);
@@ -777,9 +788,9 @@ __host__ __device__ constexpr int self_top(int lmax, bool slo) { return slo ? lm
 // FP32 sums a few 1e-5 of the largest coefficient; the recurrence is stable.
 __host__ __device__ constexpr bool direct_m(int lmax) { return lmax >= 13; }
 
-template <typename T, int LMAX, int G, bool UNIT, bool SLO = false>
-__device__ __forceinline__ void add_hit(Acc<T, LMAX, G>& A, T x, T y, T z, T w) {
-    using AC = Acc<T, LMAX, G>;
+template <bool UNIT, bool SLO, class AC, typename T = typename AC::T>
+__device__ __forceinline__ void add_hit(AC& A, T x, T y, T z, T w) {
+    constexpr int LMAX = AC::LMAX;
     constexpr int MLO = AC::MLO, MHI = AC::MHI, V0 = AC::V0;
     constexpr bool SHARE = UNIT && MLO == 0 && AC::SELF;  // s[l] == a[l] for l <= lmax
     constexpr int STOP = self_top(LMAX, SLO);
@@ -859,9 +870,10 @@ __device__ __forceinline__ void cheb_run_to_monic(const ChebTable<LMAX>& D, T* v
     }
 }
 
-template <typename T, int LMAX, int G, bool SLO = false>
-__device__ __forceinline__ void cheb_to_monic(Acc<T, LMAX, G>& A) {
-    using AC = Acc<T, LMAX, G>;
+template <bool SLO, class AC>
+__device__ __forceinline__ void cheb_to_monic(AC& A) {
+    using T = typename AC::T;
+    constexpr int LMAX = AC::LMAX;
     constexpr ChebTable<LMAX> D{};
     // with direct_m only the m = 0 sums and the self moments are Chebyshev sums
     constexpr int MTOP = direct_m(LMAX) ? 0 : AC::MHI;
@@ -875,10 +887,58 @@ __device__ __forceinline__ void cheb_to_monic(Acc<T, LMAX, G>& A) {
     if constexpr (AC::SELF) cheb_run_to_monic<T, LMAX>(D, A.s, 0, self_top(LMAX, SLO) + 1);
 }
 
-template <typename T, int LMAX, int G, bool UNIT, bool SLO>
+// A unit direction and weight.
+template <typename T> struct Dir { T x, y, z, w; };
+
+// Points of the FP64 gathers: with unit weights the weight is not loaded.
+struct Point3 { double x, y, z; };
+__device__ __forceinline__ double weight_of(const Point3&) { return 1.0; }
+__device__ __forceinline__ double weight_of(const double4& d) { return d.w; }
+
+// Direction of the minimum-image separation of two points of the box (FP64).
+// Positions lie in [0, L) and a listed pair is never half a box apart, so
+// the count of periods is -1, 0 or 1 and the product with it is exact.
+template <class Pt>
+__device__ __forceinline__ Dir<double> unit_direction(const Pt& d, const double4& P, double L, double inv_L) {
+    double dx = d.x - P.x, dy = d.y - P.y, dz = d.z - P.z;
+    dx = fma(-L, rint(dx * inv_L), dx);
+    dy = fma(-L, rint(dy * inv_L), dy);
+    dz = fma(-L, rint(dz * inv_L), dz);
+    const double r2 = dx * dx + dy * dy + dz * dz;
+    double inv = __builtin_amdgcn_rsq(r2);
+    inv = inv * fma(-0.5 * r2 * inv, inv, 1.5);
+    inv = inv * fma(-0.5 * r2 * inv, inv, 1.5);
+    return {dx * inv, dy * inv, dz * inv, weight_of(d)};
+}
+
+// End of a list's sums: the degree-0 sum is the list length with unit weights
+// (exact below 2^24 hits in FP32, and above that rounded to FP32 like any FP32
+// sum; lists hold at most 2^27), the shared self moments, the change of basis,
+// and the operand columns of primary pl. With SLO the orders above lmax are
+// zero and not stored (the self-moment sums of such a run do not read them).
+template <bool UNIT, bool SLO, class AC>
+__device__ __forceinline__ void store_sums(AC& acc, const AlmArgs& a, int b, int64_t pl, uint32_t n) {
+    using T = typename AC::T;
+    constexpr int LMAX = AC::LMAX, NV = n_values(LMAX);
+    if constexpr (UNIT && AC::MLO == 0) acc.a[0 - AC::V0] = (T)n;
+    if constexpr (UNIT && AC::MLO == 0 && AC::SELF) {
+#pragma unroll
+        for (int l = 0; l <= LMAX; ++l) acc.s[l] = acc.a[l - AC::V0];
+    }
+    cheb_to_monic<SLO>(acc);
+    T* A = reinterpret_cast<T*>(a.A);
+#pragma unroll
+    for (int i = 0; i < AC::NA; ++i) A[((int64_t)b * NV + AC::V0 + i) * a.ldA + pl] = acc.a[i];
+    if constexpr (AC::SELF) {
+#pragma unroll
+        for (int i = 0; i <= self_top(LMAX, SLO); ++i)
+            A[((int64_t)b * NV + n_alm_values(LMAX) + i) * a.ldA + pl] = acc.s[i];
+    }
+}
+
+template <int LMAX, bool UNIT, bool SLO>
 __global__ void __launch_bounds__(64) k_pair_alm(AlmArgs a) {
-    using AC = Acc<T, LMAX, G>;
-    constexpr int NV = n_values(LMAX);
+    using AC = Acc<float, LMAX, 0, UNIT, SLO>;
     // One wavefront per workgroup: 64 consecutive primaries of one bin. The
     // wavefronts of a block of 256 primaries are consecutive, bin by bin.
     const int lane = lane_id();
@@ -890,154 +950,218 @@ __global__ void __launch_bounds__(64) k_pair_alm(AlmArgs a) {
     const int rem = (int)(wv - blk * 4 * a.nb);
     const int b = rem >> 2;
     const int64_t pl = blk * 256 + (rem & 3) * 64 + lane;
-    const int64_t p = a.p_begin + pl;
     const bool active = pl < nprim;
 
     AC acc;
 #pragma unroll
-    for (int i = 0; i < (AC::NA > 0 ? AC::NA : 1); ++i) acc.a[i] = (T)0;
+    for (int i = 0; i < (AC::NA > 0 ? AC::NA : 1); ++i) acc.a[i] = 0.f;
 #pragma unroll
-    for (int i = 0; i < (AC::NS > 0 ? AC::NS : 1); ++i) acc.s[i] = (T)0;
+    for (int i = 0; i < (AC::NS > 0 ? AC::NS : 1); ++i) acc.s[i] = 0.f;
 
     uint32_t n = 0, off = 0;
     if (active) {
         n = a.cnt[pl * a.nb + b];
         off = a.boff[pl * a.nb + b];
     }
-    if constexpr (sizeof(T) == 4) {
-        // FP32: the binning pass wrote each hit as (dx, dy, dz, w_j), or
-        // with unit weights as the octahedral code of its direction. Two
-        // sets of K records per lane in ping-pong: each half of an iteration
-        // first refills the other set with the next K records, then
-        // accumulates its own set, loaded one half earlier. The loads are
-        // unconditional (at a clamped index past the end of the list), so the
-        // loads in flight are the same on every path: the wait before a set
-        // is used covers exactly that set, loaded a whole half (K hits of
-        // arithmetic) before. (Conditional loads, or rotating registers,
-        // would make every hit wait for the newest load.) Four records per
-        // set, eight where the sums alone take more than 128 registers: such
-        // a lane runs at two waves per SIMD, and a set of eight 16-byte
-        // records is a whole 128-byte line of its list (with four, the two
-        // halves of a line are fetched a set apart, and were measured slower
-        // even at three waves). With 8-byte codes, sets of sixteen (whole
-        // lines again) were measured slower than sets of eight.
-        constexpr int K = AC::NA + AC::NS > 128 ? 8 : 4;
-        // an empty list reads the first record of the buffer (not accumulated)
-        const size_t roff = n > 0 ? 4 * (size_t)off : 0;  // offsets count blocks of four records
-        const uint32_t last = n > 0 ? n - 1 : 0;
-        // with UNIT the records are the 8-byte direction codes (p, q)
-        const float4* rec = a.rec + roff;
-        const float2* rec2 = reinterpret_cast<const float2*>(a.rec) + roff;
-        using RecT = std::conditional_t<UNIT, float2, float4>;
-        auto load_rec = [&](uint32_t i) -> RecT {
-            if constexpr (UNIT) {
-                return rec2[i];
-            } else {
-                return rec[i];
-            }
-        };
-        RecT qa[K], qb[K];
-#pragma unroll
-        for (int i = 0; i < K; ++i) qa[i] = load_rec(min((uint32_t)i, last));
-        auto hit = [&](const RecT q) {
-            if constexpr (UNIT) {
-                const float3 d = oct_decode(q.x, q.y);
-                const float inv = __builtin_amdgcn_rsqf(d.x * d.x + d.y * d.y + d.z * d.z);
-                add_hit<T, LMAX, G, UNIT, SLO>(acc, d.x * inv, d.y * inv, d.z * inv, 1.f);
-            } else {
-                const float d2 = q.x * q.x + q.y * q.y + q.z * q.z;
-                const float inv = __builtin_amdgcn_rsqf(d2);
-                add_hit<T, LMAX, G, UNIT, SLO>(acc, q.x * inv, q.y * inv, q.z * inv, q.w);
-            }
-        };
-        for (uint32_t t = 0; t < n; t += 2 * K) {
-#pragma unroll
-            for (int i = 0; i < K; ++i) qb[i] = load_rec(min(t + K + i, last));
-#pragma unroll
-            for (int i = 0; i < K; ++i)
-                if (t + i < n) hit(qa[i]);
-#pragma unroll
-            for (int i = 0; i < K; ++i) qa[i] = load_rec(min(t + 2 * K + i, last));
-#pragma unroll
-            for (int i = 0; i < K; ++i)
-                if (t + K + i < n) hit(qb[i]);
+    // FP32: the binning pass wrote each hit as (dx, dy, dz, w_j), or
+    // with unit weights as the octahedral code of its direction. Two
+    // sets of K records per lane in ping-pong: each half of an iteration
+    // first refills the other set with the next K records, then
+    // accumulates its own set, loaded one half earlier. The loads are
+    // unconditional (at a clamped index past the end of the list), so the
+    // loads in flight are the same on every path: the wait before a set
+    // is used covers exactly that set, loaded a whole half (K hits of
+    // arithmetic) before. (Conditional loads, or rotating registers,
+    // would make every hit wait for the newest load.) Four records per
+    // set, eight where the sums alone take more than 128 registers: such
+    // a lane runs at two waves per SIMD, and a set of eight 16-byte
+    // records is a whole 128-byte line of its list (with four, the two
+    // halves of a line are fetched a set apart, and were measured slower
+    // even at three waves). With 8-byte codes, sets of sixteen (whole
+    // lines again) were measured slower than sets of eight.
+    constexpr int K = AC::NA + AC::NS > 128 ? 8 : 4;
+    // an empty list reads the first record of the buffer (not accumulated)
+    const size_t roff = n > 0 ? 4 * (size_t)off : 0;  // offsets count blocks of four records
+    const uint32_t last = n > 0 ? n - 1 : 0;
+    const float4* rec = a.rec + roff;
+    const float2* rec2 = reinterpret_cast<const float2*>(a.rec) + roff;
+    using RecT = std::conditional_t<UNIT, float2, float4>;
+    auto load_rec = [&](uint32_t i) -> RecT {
+        if constexpr (UNIT) {
+            return rec2[i];
+        } else {
+            return rec[i];
         }
-    } else {
-        // FP64: the lane gathers its neighbours through the list entries,
-        // with the same ping-pong of unconditional loads as the FP32 path in
-        // two stages: a set's entries are loaded one half before its points
-        // are gathered, and the points one half before they are accumulated.
-        // A slot past the end of the list gathers the primary itself (not
-        // accumulated), so every address is valid. The gathers are
-        // latency-bound: the kernels that split the m range (lmax >= 7, two
-        // waves per SIMD or one) keep six entries and points per set in
-        // flight (lmax 10: 360 ms per step with two, 320 with three, 287 with
-        // four, 274 with six or eight).
-        constexpr int K = G == 0 ? 2 : 6;
-        const int64_t pself = active ? p : a.p_begin;
-        const int64_t cstart = a.pt_off[a.catid[pself]];
-        const double4 P64 = a.pd[pself];
-        const uint32_t mask = a.g.idx_mask;
-        const uint32_t* lst = n > 0 ? a.list + 4 * (size_t)off : a.list;  // offsets count blocks of four entries
-        const uint32_t last = n > 0 ? n - 1 : 0;
-        auto entry = [&](uint32_t r) { return lst[min(r, last)]; };
-        auto gather = [&](uint32_t r, uint32_t e) { return a.pd[r < n ? cstart + (int64_t)(e & mask) : pself]; };
-        auto hit = [&](const double4 d) {
-            double dx = d.x - P64.x, dy = d.y - P64.y, dz = d.z - P64.z;
-            const double L = a.g.box, hL = 0.5 * a.g.box;
-            dx = dx > hL ? dx - L : (dx < -hL ? dx + L : dx);
-            dy = dy > hL ? dy - L : (dy < -hL ? dy + L : dy);
-            dz = dz > hL ? dz - L : (dz < -hL ? dz + L : dz);
-            const double r2 = dx * dx + dy * dy + dz * dz;
-            double inv = __builtin_amdgcn_rsq(r2);
-            inv = inv * fma(-0.5 * r2 * inv, inv, 1.5);
-            inv = inv * fma(-0.5 * r2 * inv, inv, 1.5);
-            add_hit<T, LMAX, G, UNIT, SLO>(acc, (T)(dx * inv), (T)(dy * inv), (T)(dz * inv), (T)d.w);
-        };
-        uint32_t ea[K], eb[K];
-        double4 da[K], db[K];
+    };
+    RecT qa[K], qb[K];
 #pragma unroll
-        for (int i = 0; i < K; ++i) ea[i] = entry((uint32_t)i);
-#pragma unroll
-        for (int i = 0; i < K; ++i) da[i] = gather((uint32_t)i, ea[i]);
-#pragma unroll
-        for (int i = 0; i < K; ++i) eb[i] = entry((uint32_t)(K + i));
-        for (uint32_t t = 0; t < n; t += 2 * K) {
-#pragma unroll
-            for (int i = 0; i < K; ++i) db[i] = gather(t + K + i, eb[i]);
-#pragma unroll
-            for (int i = 0; i < K; ++i) ea[i] = entry(t + 2 * K + i);
-#pragma unroll
-            for (int i = 0; i < K; ++i)
-                if (t + i < n) hit(da[i]);
-#pragma unroll
-            for (int i = 0; i < K; ++i) da[i] = gather(t + 2 * K + i, ea[i]);
-#pragma unroll
-            for (int i = 0; i < K; ++i) eb[i] = entry(t + 3 * K + i);
-#pragma unroll
-            for (int i = 0; i < K; ++i)
-                if (t + K + i < n) hit(db[i]);
+    for (int i = 0; i < K; ++i) qa[i] = load_rec(min((uint32_t)i, last));
+    auto hit = [&](const RecT q) {
+        if constexpr (UNIT) {
+            const float3 d = oct_decode(q.x, q.y);
+            const float inv = __builtin_amdgcn_rsqf(d.x * d.x + d.y * d.y + d.z * d.z);
+            add_hit<UNIT, SLO>(acc, d.x * inv, d.y * inv, d.z * inv, 1.f);
+        } else {
+            const float d2 = q.x * q.x + q.y * q.y + q.z * q.z;
+            const float inv = __builtin_amdgcn_rsqf(d2);
+            add_hit<UNIT, SLO>(acc, q.x * inv, q.y * inv, q.z * inv, q.w);
         }
+    };
+    for (uint32_t t = 0; t < n; t += 2 * K) {
+#pragma unroll
+        for (int i = 0; i < K; ++i) qb[i] = load_rec(min(t + K + i, last));
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+            if (t + i < n) hit(qa[i]);
+#pragma unroll
+        for (int i = 0; i < K; ++i) qa[i] = load_rec(min(t + 2 * K + i, last));
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+            if (t + K + i < n) hit(qb[i]);
     }
-    if (!active) return;
-    // the degree-0 sum is the list length: exact below 2^24 hits in FP32, and
-    // above that rounded to FP32 like any FP32 sum (lists hold at most 2^27)
-    if constexpr (UNIT && AC::MLO == 0) acc.a[0 - AC::V0] = (T)n;
-    if constexpr (UNIT && AC::MLO == 0 && AC::SELF) {
+    if (active) store_sums<UNIT, SLO>(acc, a, b, pl, n);
+}
+
+// The FP64 path, and the m range in parts (FP32 above lmax 10, FP64 above 6):
+// one workgroup per 64 lists, a wavefront per part, the lane of a list in each. A set of K hits
+// of every list is brought in together: each wavefront reads KG of them
+// (records, or FP64 points through the list entries), forms their directions
+// and leaves them in LDS, and after a barrier every wavefront adds all K to
+// its part of the orders. The reads of the next set are issued before, its
+// directions formed after the sums of the current one; two LDS buffers, one
+// barrier per set.
+// A load whose lanes read 64 lists touches 64 cache lines, one per cycle, so
+// the FP64 gathers (two loads and an entry per hit) are what bounds that path
+// when every part makes its own. FP64, ten catalogues of 1.2e5 points, 10 bins:
+// lmax 10 18.7 ms with a launch per part and 304 registers (one wavefront per
+// SIMD), 12.6 ms with this kernel (226 registers, two); lmax 4 9.2 and 7.0 ms
+// (one part: the wide entry loads and the deeper set). FP32 at 30,011 points and
+// 7 bins: lmax 13 0.64 ms with three launches, 0.41 ms with two parts here;
+// lmax 16 0.85 and 0.55 ms with three.
+__host__ __device__ constexpr int part_set(int np) { return np <= 2 ? 4 : 2; }  // KG
+
+template <typename T, int LMAX, int G0, int NP, int P, bool UNIT, bool SLO>
+__device__ __forceinline__ void alm_part(const AlmArgs& a, T* smem) {
+    using AC = Acc<T, LMAX, G0 + P, UNIT, SLO>;
+    constexpr bool F64 = sizeof(T) == 8;
+    constexpr int KG = part_set(NP), K = KG * NP, NC = UNIT ? 3 : 4;
+    const int lane = lane_id();
+    const int64_t nprim = a.p_end - a.p_begin;
+    // blocks of 256 primaries, bin by bin, 64 lists each (as k_pair_alm)
+    const int64_t wv = xcd_block(blockIdx.x, (int64_t)gridDim.x);
+    const int64_t blk = wv / (4 * a.nb);
+    const int rem = (int)(wv - blk * 4 * a.nb);
+    const int b = rem >> 2;
+    const int64_t pl = blk * 256 + (rem & 3) * 64 + lane;
+    const bool active = pl < nprim;
+    AC acc;
 #pragma unroll
-        for (int l = 0; l <= LMAX; ++l) acc.s[l] = acc.a[l - AC::V0];
+    for (int i = 0; i < (AC::NA > 0 ? AC::NA : 1); ++i) acc.a[i] = (T)0;
+#pragma unroll
+    for (int i = 0; i < (AC::NS > 0 ? AC::NS : 1); ++i) acc.s[i] = (T)0;
+    uint32_t n = 0, off = 0;
+    if (active) {
+        n = a.cnt[pl * a.nb + b];
+        off = a.boff[pl * a.nb + b];
     }
-    cheb_to_monic<T, LMAX, G, SLO>(acc);
-    T* A = reinterpret_cast<T*>(a.A);
-    const int64_t ld = a.ldA;
+    uint32_t nmax = n;
+    for (int o = 32; o > 0; o >>= 1) nmax = max(nmax, (uint32_t)__shfl_xor((int)nmax, o, 64));
+    nmax = __builtin_amdgcn_readfirstlane(nmax);
+    const uint32_t last = n > 0 ? n - 1 : 0;
+    const size_t base = n > 0 ? 4 * (size_t)off : 0;  // an empty list reads the buffer's start
+
+    // hits KG P .. KG P + KG - 1 of a set, of every list
+    const int64_t pself = active ? a.p_begin + pl : a.p_begin;
+    using Src = std::conditional_t<F64, std::conditional_t<UNIT, Point3, double4>, float4>;
+    Src src[KG];
+    uint32_t ent[KG];
+    int64_t cstart = 0;
+    double4 P64 = make_double4(0.0, 0.0, 0.0, 0.0);
+    if constexpr (F64) {
+        cstart = a.pt_off[a.catid[pself]];
+        P64 = a.pd[pself];
+    }
+    // The entries of KG hits are one load (lists start at multiples of four
+    // and their room is one too, so the load stays inside it); past the end of
+    // a list its last ones are read again.
+    auto entries = [&](uint32_t t) {
+        if constexpr (F64) {
+            const uint32_t r = min(t + KG * P, last & ~(uint32_t)(KG - 1));
+            __builtin_memcpy(ent, __builtin_assume_aligned(a.list + base + r, 4 * KG), 4 * KG);
+        }
+    };
+    auto fetch = [&](uint32_t t) {
 #pragma unroll
-    for (int i = 0; i < AC::NA; ++i) A[((int64_t)b * NV + AC::V0 + i) * ld + pl] = acc.a[i];
-    if constexpr (AC::SELF) {
-        // with SLO the orders above lmax are zero and not stored (the
-        // self-moment sums of such a run do not read them)
+        for (int i = 0; i < KG; ++i) {
+            const uint32_t r = t + KG * P + i;
+            if constexpr (F64)
+                src[i] = *reinterpret_cast<const Src*>(
+                    a.pd + (r < n ? cstart + (int64_t)(ent[i] & a.g.idx_mask) : pself));
+            else
+                src[i] = a.rec[base + min(r, last)];
+        }
+    };
+    auto publish = [&](T* buf) {
 #pragma unroll
-        for (int i = 0; i <= self_top(LMAX, SLO); ++i)
-            A[((int64_t)b * NV + n_alm_values(LMAX) + i) * ld + pl] = acc.s[i];
+        for (int i = 0; i < KG; ++i) {
+            Dir<T> u;
+            if constexpr (F64) {
+                u = unit_direction(src[i], P64, a.g.box, 1.0 / a.g.box);
+            } else {
+                const float inv = __builtin_amdgcn_rsqf(src[i].x * src[i].x + src[i].y * src[i].y + src[i].z * src[i].z);
+                u = {src[i].x * inv, src[i].y * inv, src[i].z * inv, src[i].w};
+            }
+            T* at = buf + (KG * P + i) * NC * 64 + lane;
+            at[0] = u.x;
+            at[64] = u.y;
+            at[128] = u.z;
+            if constexpr (!UNIT) at[192] = u.w;
+        }
+    };
+    entries(0);
+    fetch(0);
+    entries(K);
+    int buf = 0;
+    for (uint32_t t = 0; t < nmax; t += K) {
+        T* cur = smem + buf * K * NC * 64;
+        publish(cur);
+        __syncthreads();
+        fetch(t + K);
+        entries(t + 2 * K);
+        // a hit's direction is read, by every lane, while the one before adds
+        auto take = [&](int i) {
+            const T* at = cur + i * NC * 64 + lane;
+            Dir<T> u{at[0], at[64], at[128], (T)1};
+            if constexpr (!UNIT) u.w = at[192];
+            return u;
+        };
+        Dir<T> next = take(0);
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            const Dir<T> u = next;
+            if (i + 1 < K) next = take(i + 1);
+            if (t + i < n) add_hit<UNIT, SLO>(acc, u.x, u.y, u.z, u.w);
+        }
+        buf ^= 1;
+    }
+    if (active) store_sums<UNIT, SLO>(acc, a, b, pl, n);
+}
+
+template <typename T, int LMAX, int G0, int NP, bool UNIT, bool SLO>
+__global__ void __launch_bounds__(64 * NP) k_pair_alm_parts(AlmArgs a) {
+    __shared__ T smem[2 * part_set(NP) * NP * (UNIT ? 3 : 4) * 64];
+    const int64_t nwaves = ((a.p_end - a.p_begin + 255) / 256) * a.nb * 4;
+    if (xcd_block(blockIdx.x, (int64_t)gridDim.x) >= nwaves) return;
+    const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (part == 0) alm_part<T, LMAX, G0, NP, 0, UNIT, SLO>(a, smem);
+    if constexpr (NP > 1) {
+        if (part == 1) alm_part<T, LMAX, G0, NP, 1, UNIT, SLO>(a, smem);
+    }
+    if constexpr (NP > 2) {
+        if (part == 2) alm_part<T, LMAX, G0, NP, 2, UNIT, SLO>(a, smem);
+    }
+    if constexpr (NP > 3) {
+        if (part == 3) alm_part<T, LMAX, G0, NP, 3, UNIT, SLO>(a, smem);
     }
 }
 
@@ -1052,7 +1176,7 @@ constexpr int kWaveListWaves = 4;
 
 template <int LMAX, bool UNIT, bool SLO>
 __global__ void __launch_bounds__(64 * kWaveListWaves) k_pair_alm_wave(AlmArgs a) {
-    using AC = Acc<float, LMAX, 0>;
+    using AC = Acc<float, LMAX, 0, UNIT, SLO>;
     constexpr int NV = n_values(LMAX);
     const int lane = lane_id();
     const int64_t nprim = a.p_end - a.p_begin;
@@ -1089,11 +1213,11 @@ __global__ void __launch_bounds__(64 * kWaveListWaves) k_pair_alm_wave(AlmArgs a
         if constexpr (UNIT) {
             const float3 d = oct_decode(q.x, q.y);
             const float inv = __builtin_amdgcn_rsqf(d.x * d.x + d.y * d.y + d.z * d.z);
-            add_hit<float, LMAX, 0, UNIT, SLO>(acc, d.x * inv, d.y * inv, d.z * inv, 1.f);
+            add_hit<UNIT, SLO>(acc, d.x * inv, d.y * inv, d.z * inv, 1.f);
         } else {
             const float d2 = q.x * q.x + q.y * q.y + q.z * q.z;
             const float inv = __builtin_amdgcn_rsqf(d2);
-            add_hit<float, LMAX, 0, UNIT, SLO>(acc, q.x * inv, q.y * inv, q.z * inv, q.w);
+            add_hit<UNIT, SLO>(acc, q.x * inv, q.y * inv, q.z * inv, q.w);
         }
     };
     for (uint32_t t0 = 0; t0 < n; t0 += 128 * K) {
@@ -1124,7 +1248,7 @@ __global__ void __launch_bounds__(64 * kWaveListWaves) k_pair_alm_wave(AlmArgs a
         for (int i = 0; i <= self_top(LMAX, SLO); ++i)
             for (int o = 32; o > 0; o >>= 1) acc.s[i] += __shfl_xor(acc.s[i], o, 64);
     }
-    cheb_to_monic<float, LMAX, 0, SLO>(acc);
+    cheb_to_monic<SLO>(acc);
     // lane i writes value i
     float* A = reinterpret_cast<float*>(a.A);
     const int64_t ld = a.ldA;
@@ -1136,68 +1260,57 @@ __global__ void __launch_bounds__(64 * kWaveListWaves) k_pair_alm_wave(AlmArgs a
         if (lane == (AC::NA + i) % 64) A[((int64_t)b * NV + n_alm_values(LMAX) + i) * ld + pl] = acc.s[i];
 }
 
-template <typename T, int LMAX, int G>
-hipError_t launch_alm_one(const AlmArgs& a, hipStream_t s) {
+// UNIT: all weights 1, the m = 0 sums are shared with the self moments.
+template <int LMAX, bool UNIT>
+hipError_t launch_alm_whole(const AlmArgs& a, hipStream_t s) {
     const int64_t nprim = a.p_end - a.p_begin;
-    if constexpr (sizeof(T) == 4 && G == 0 && LMAX <= 6) {
+    if constexpr (LMAX <= 6) {
         if (a.wave_per_list) {
             const int64_t nw = (nprim * a.nb + kWaveListWaves - 1) / kWaveListWaves;
             const int64_t nwg = (nw + 7) / 8 * 8;
             const dim3 grid((unsigned)nwg), block(64 * kWaveListWaves);
-            if (a.unit_w) {
-                if (a.self_lo) hipLaunchKernelGGL((k_pair_alm_wave<LMAX, true, true>), grid, block, 0, s, a);
-                else hipLaunchKernelGGL((k_pair_alm_wave<LMAX, true, false>), grid, block, 0, s, a);
-            } else {
-                if (a.self_lo) hipLaunchKernelGGL((k_pair_alm_wave<LMAX, false, true>), grid, block, 0, s, a);
-                else hipLaunchKernelGGL((k_pair_alm_wave<LMAX, false, false>), grid, block, 0, s, a);
-            }
+            if (a.self_lo) hipLaunchKernelGGL((k_pair_alm_wave<LMAX, UNIT, true>), grid, block, 0, s, a);
+            else hipLaunchKernelGGL((k_pair_alm_wave<LMAX, UNIT, false>), grid, block, 0, s, a);
             return hipGetLastError();
         }
     }
     const int64_t nwaves = ((nprim + 255) / 256) * a.nb * 4;
-    const int64_t nwg = (nwaves + 7) / 8 * 8;
-    const dim3 grid((unsigned)nwg), block(64);
-    if constexpr (sizeof(T) == 4 && G == 0) {
-        // unit weights: the FP32 single-launch kernel shares the m = 0 sums;
-        // self_lo: the self moments stop at order lmax
-        if (a.unit_w) {
-            if (a.self_lo) hipLaunchKernelGGL((k_pair_alm<T, LMAX, G, true, true>), grid, block, 0, s, a);
-            else hipLaunchKernelGGL((k_pair_alm<T, LMAX, G, true, false>), grid, block, 0, s, a);
-        } else {
-            if (a.self_lo) hipLaunchKernelGGL((k_pair_alm<T, LMAX, G, false, true>), grid, block, 0, s, a);
-            else hipLaunchKernelGGL((k_pair_alm<T, LMAX, G, false, false>), grid, block, 0, s, a);
-        }
-    } else {
-        hipLaunchKernelGGL((k_pair_alm<T, LMAX, G, false, false>), grid, block, 0, s, a);
-    }
+    const dim3 grid((unsigned)((nwaves + 7) / 8 * 8)), block(64);
+    // self_lo: the self moments stop at order lmax
+    if (a.self_lo) hipLaunchKernelGGL((k_pair_alm<LMAX, UNIT, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_pair_alm<LMAX, UNIT, false>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 
-// FP32 keeps every value of a bin in one lane up to lmax 10, and splits the
-// m range over two launches at lmax 11 and 12 and three from 13; FP64 splits
-// it over two launches from lmax 7 and four from 13 (register budget). Every
-// launch rereads the lists.
-template <typename T, int LMAX, int G0, int NP>
+template <typename T, int LMAX, int G0, int NP, bool UNIT>
 hipError_t launch_alm_parts(const AlmArgs& a, hipStream_t s) {
-    hipError_t e = launch_alm_one<T, LMAX, G0>(a, s);
-    if constexpr (NP > 1) {
-        if (e != hipSuccess) return e;
-        return launch_alm_parts<T, LMAX, G0 + 1, NP - 1>(a, s);
+    const int64_t nwaves = ((a.p_end - a.p_begin + 255) / 256) * a.nb * 4;
+    const dim3 grid((unsigned)((nwaves + 7) / 8 * 8)), block(64 * NP);
+    if (a.self_lo) hipLaunchKernelGGL((k_pair_alm_parts<T, LMAX, G0, NP, UNIT, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_pair_alm_parts<T, LMAX, G0, NP, UNIT, false>), grid, block, 0, s, a);
+    return hipGetLastError();
+}
+
+// FP32 keeps every value of a bin in one lane up to lmax 10 and splits the m
+// range in two parts to lmax 14 and three above; FP64 in two parts from lmax
+// 7 and four from 13 (register budget).
+constexpr int kTwoParts32 = 14;
+template <int LMAX, bool UNIT>
+hipError_t launch_alm_lmax(const AlmArgs& a, int fp64, hipStream_t s) {
+    if (!fp64) {
+        if constexpr (LMAX <= 10) return launch_alm_whole<LMAX, UNIT>(a, s);
+        else if constexpr (LMAX <= kTwoParts32) return launch_alm_parts<float, LMAX, 1, 2, UNIT>(a, s);
+        else return launch_alm_parts<float, LMAX, 3, 3, UNIT>(a, s);
+    } else {
+        if constexpr (LMAX <= 6) return launch_alm_parts<double, LMAX, 0, 1, UNIT>(a, s);
+        else if constexpr (LMAX <= 12) return launch_alm_parts<double, LMAX, 1, 2, UNIT>(a, s);
+        else return launch_alm_parts<double, LMAX, 6, 4, UNIT>(a, s);
     }
-    return e;
 }
 
 template <int LMAX>
-hipError_t launch_alm_lmax(const AlmArgs& a, int fp64, hipStream_t s) {
-    if (!fp64) {
-        if constexpr (LMAX <= 10) return launch_alm_one<float, LMAX, 0>(a, s);
-        else if constexpr (LMAX <= 12) return launch_alm_parts<float, LMAX, 1, 2>(a, s);
-        else return launch_alm_parts<float, LMAX, 3, 3>(a, s);
-    } else {
-        if constexpr (LMAX <= 6) return launch_alm_one<double, LMAX, 0>(a, s);
-        else if constexpr (LMAX <= 12) return launch_alm_parts<double, LMAX, 1, 2>(a, s);
-        else return launch_alm_parts<double, LMAX, 6, 4>(a, s);
-    }
+hipError_t launch_alm_weights(const AlmArgs& a, int fp64, hipStream_t s) {
+    return a.unit_w ? launch_alm_lmax<LMAX, true>(a, fp64, s) : launch_alm_lmax<LMAX, false>(a, fp64, s);
 }
 
 }  // namespace
@@ -1242,23 +1355,23 @@ hipError_t launch_pair_fix(const BinArgs& a, hipStream_t s) {
 hipError_t launch_pair_alm(const AlmArgs& a, int fp64, hipStream_t s) {
     if (a.p_end <= a.p_begin) return hipSuccess;
     switch (a.lmax) {
-        case 0: return launch_alm_lmax<0>(a, fp64, s);
-        case 1: return launch_alm_lmax<1>(a, fp64, s);
-        case 2: return launch_alm_lmax<2>(a, fp64, s);
-        case 3: return launch_alm_lmax<3>(a, fp64, s);
-        case 4: return launch_alm_lmax<4>(a, fp64, s);
-        case 5: return launch_alm_lmax<5>(a, fp64, s);
-        case 6: return launch_alm_lmax<6>(a, fp64, s);
-        case 7: return launch_alm_lmax<7>(a, fp64, s);
-        case 8: return launch_alm_lmax<8>(a, fp64, s);
-        case 9: return launch_alm_lmax<9>(a, fp64, s);
-        case 10: return launch_alm_lmax<10>(a, fp64, s);
-        case 11: return launch_alm_lmax<11>(a, fp64, s);
-        case 12: return launch_alm_lmax<12>(a, fp64, s);
-        case 13: return launch_alm_lmax<13>(a, fp64, s);
-        case 14: return launch_alm_lmax<14>(a, fp64, s);
-        case 15: return launch_alm_lmax<15>(a, fp64, s);
-        case 16: return launch_alm_lmax<16>(a, fp64, s);
+        case 0: return launch_alm_weights<0>(a, fp64, s);
+        case 1: return launch_alm_weights<1>(a, fp64, s);
+        case 2: return launch_alm_weights<2>(a, fp64, s);
+        case 3: return launch_alm_weights<3>(a, fp64, s);
+        case 4: return launch_alm_weights<4>(a, fp64, s);
+        case 5: return launch_alm_weights<5>(a, fp64, s);
+        case 6: return launch_alm_weights<6>(a, fp64, s);
+        case 7: return launch_alm_weights<7>(a, fp64, s);
+        case 8: return launch_alm_weights<8>(a, fp64, s);
+        case 9: return launch_alm_weights<9>(a, fp64, s);
+        case 10: return launch_alm_weights<10>(a, fp64, s);
+        case 11: return launch_alm_weights<11>(a, fp64, s);
+        case 12: return launch_alm_weights<12>(a, fp64, s);
+        case 13: return launch_alm_weights<13>(a, fp64, s);
+        case 14: return launch_alm_weights<14>(a, fp64, s);
+        case 15: return launch_alm_weights<15>(a, fp64, s);
+        case 16: return launch_alm_weights<16>(a, fp64, s);
         default: return hipErrorInvalidValue;
     }
 }

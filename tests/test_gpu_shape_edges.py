@@ -281,3 +281,43 @@ def test_separations_around_edges(torch, box, refine, prec, weighted):
     ref, _, res = O.run(pos, box, edges, 0, [(0, 0, 0)])
     assert pairs == res.npairs
     assert np.abs(got - ref).max() <= 1e-12 * np.abs(ref).max()
+
+
+# one part (lmax 0, 6), two (7, 12), four (13) in FP64; two (11, 14) and three
+# (15, 16) in FP32
+@pytest.mark.parametrize("prec,lmax", [(T.PREC_FP64, 0), (T.PREC_FP64, 6), (T.PREC_FP64, 7), (T.PREC_FP64, 12),
+                                       (T.PREC_FP64, 13), (T.PREC_FP32, 11), (T.PREC_FP32, 14), (T.PREC_FP32, 15),
+                                       (T.PREC_FP32, 16)])
+@pytest.mark.parametrize("weighted", [False, True])
+def test_parts_list_lengths(torch, prec, lmax, weighted):
+    """Lists of 0 to 33 hits (below, at and above the sets the parts bring in
+    together), clusters far apart and one across the box's corner: a_lm as the
+    oracle's (1e-12 of the largest in FP64, 1e-5 in FP32), and a batched run
+    (self moments to order lmax) gives the step calls' multipoles bit for bit."""
+    rng = np.random.default_rng(lmax)
+    box, edges = 300.0, np.array([2.0, 6.0, 9.0])
+    pos, w = [], []
+    for i, k in enumerate([0, 1, 2, 3, 4, 5, 7, 8, 9, 11, 12, 13, 15, 16, 17, 33]):
+        c = np.array([60.0 * (i % 4), 60.0 * (i // 4), 30.0 * (i % 3)])
+        d = rng.standard_normal((k, 3))
+        d *= (rng.uniform(2.1, 5.9, k) / np.linalg.norm(d, axis=1))[:, None]
+        pos += [c[None, :], c + d]
+        w.append(rng.uniform(-1.0, 1.0, k + 1))
+    pos, w = np.mod(np.vstack(pos), box), np.concatenate(w)
+    n = len(pos)
+    say(f"  parts: lmax={lmax} prec={prec} weighted={weighted}")
+    P, W = torch.from_numpy(pos).cuda(), torch.from_numpy(w).cuda() if weighted else None
+    h = T.Handle(box, edges, lmax, precision=prec)
+    h.build_grid(P, W, n)
+    h.alm_accumulate()
+    alm = h.get_alm(0, n).cpu().numpy()
+    h.contract()
+    mults = O.all_multipoles(lmax, min(lmax, 2))
+    steps = h.multipoles(mults).cpu().numpy()
+    batched = h.run_catalogs([n], [n], P, W, mults)[0].cpu().numpy()
+    h.close()
+    assert np.array_equal(steps, batched)
+    ref = O.estimate(pos, box, edges, lmax, w=w if weighted else None, want_alm=True).alm
+    mask = np.tril(np.ones((lmax + 1, lmax + 1), dtype=bool))
+    off = np.abs(alm[..., mask] - ref[..., mask]).max() / np.abs(ref).max()
+    assert off <= (1e-12 if prec == T.PREC_FP64 else 1e-5), off
