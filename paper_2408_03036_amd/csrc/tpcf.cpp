@@ -11,9 +11,11 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <string>
 #include <unordered_set>
+#include <utility>
 #include <vector>
 
 #include "../../include/tpcf.h"
@@ -34,6 +36,7 @@ const double kPi = 3.14159265358979323846;
 struct DevBuf {
     void* p = nullptr;
     size_t bytes = 0;
+    std::vector<unsigned char> held;  // a table as last uploaded (empty: not known)
 };
 
 struct Timer {
@@ -87,9 +90,15 @@ struct tpcf_handle_s {
     int couple = -1;        // this pass's contraction may skip blocks with |l1 - l2| > couple (-1: none)
     int couple_cut = -1;    // the summed blocks stop at |l1 - l2| <= couple_cut (set by tpcf_run_catalogs)
     DevBuf d_pt_off, d_cellid, d_count, d_start, d_slab, d_cursor, d_tmp, d_tmpz, d_orig, d_pf, d_pw, d_pa, d_pd, d_perm,
-        d_catid, d_flag, d_istart, d_icell, d_icat, d_scanw, d_catbad;
+        d_catid, d_flag, d_istart, d_icell, d_scanw, d_catbad;
     std::vector<int32_t> cat_status;  // per catalogue of the last tpcf_run_catalogs
     std::vector<int> item_cat;       // [ncat+1] first work item of each catalogue
+    int nonfinite = 0;               // non-finite positions of the grid's points
+    // Pinned memory that kernels write what the host reads to: ints 0 .. 3 the
+    // flags of a pass, then a grid's count of non-finite positions and item_cat.
+    int* host = nullptr;
+    int* host_dev = nullptr;         // its device address
+    size_t host_ints = 0;
 
     // pair pass
     std::vector<int64_t> sub_start;  // global subchunks (sorted index of first primary), + end
@@ -174,6 +183,7 @@ tpcf_status ensure(tpcf_handle h, DevBuf& b, size_t bytes) {
         h->used -= (int64_t)b.bytes;
         b.p = nullptr;
         b.bytes = 0;
+        b.held.clear();
     }
     if (bytes == 0) bytes = 256;
     bytes = (bytes + 255) / 256 * 256;
@@ -190,13 +200,83 @@ tpcf_status ensure(tpcf_handle h, DevBuf& b, size_t bytes) {
     return TPCF_OK;
 }
 
-// Stream-ordered copy of a small host table; waits for it so that the host
-// memory may be released and the table is never overwritten under a kernel.
+// Stream-ordered copy of a small host table. A call uploads about ten, most of
+// them equal to what the handle uploaded for the call before (the stencil, the
+// guard bands, the coefficients of the multipoles), and every copy was waited
+// for: 0.15 ms of a call of 2,000 points that takes 0.32. Now a table whose
+// bytes are those the buffer holds is left (nothing but uploads write these
+// buffers), one of up to kPutMax bytes is put there by kernels that carry it in
+// their arguments, so that the host memory is free at once, and only a larger
+// one is copied and waited for.
+constexpr size_t kPutMax = 4 * sizeof(uint32_t) * kPutWords;
+constexpr size_t kHeldMax = 1 << 18;  // bytes of a table kept for the comparison
+
 tpcf_status upload(tpcf_handle h, DevBuf& b, const void* src, size_t bytes) {
     tpcf_status st = ensure(h, b, bytes);
     if (st != TPCF_OK) return st;
-    HIPCHK(hipMemcpyAsync(b.p, src, bytes, hipMemcpyHostToDevice, h->stream));
+    // A capture would record the launches without running them: it takes the
+    // copy and its wait, which refuse it.
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const bool live = hipStreamIsCapturing(h->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+    if (live && bytes > 0 && b.held.size() == bytes && std::memcmp(b.held.data(), src, bytes) == 0) return TPCF_OK;
+    b.held.clear();
+    if (live && bytes <= kPutMax && bytes % sizeof(uint32_t) == 0) {
+        PutWords w;
+        for (size_t o = 0; o < bytes; o += sizeof(w.v)) {
+            const size_t n = std::min(bytes - o, sizeof(w.v));
+            std::memcpy(w.v, static_cast<const unsigned char*>(src) + o, n);
+            HIPCHK(launch_put(reinterpret_cast<uint32_t*>(b.p) + o / sizeof(uint32_t), (int)(n / sizeof(uint32_t)), w,
+                              h->stream));
+        }
+    } else {
+        HIPCHK(hipMemcpyAsync(b.p, src, bytes, hipMemcpyHostToDevice, h->stream));
+        HIPCHK(hipStreamSynchronize(h->stream));
+    }
+    if (bytes <= kHeldMax)
+        b.held.assign(static_cast<const unsigned char*>(src), static_cast<const unsigned char*>(src) + bytes);
+    return TPCF_OK;
+}
+
+// At least n ints of pinned memory that kernels of the handle's stream write.
+tpcf_status ensure_host(tpcf_handle h, size_t n) {
+    if (h->host_ints >= n) return TPCF_OK;
+    if (h->host) {
+        HIPCHK(hipStreamSynchronize(h->stream));  // no kernel still writes there
+        hipHostFree(h->host);
+        h->host = h->host_dev = nullptr;
+        h->host_ints = 0;
+    }
+    n = std::max<size_t>(n, 256);
+    void* p = nullptr;
+    const hipError_t e = hipHostMalloc(&p, n * sizeof(int), hipHostMallocMapped);
+    if (e != hipSuccess) return fail(h, TPCF_ERR_ALLOC, std::string("hipHostMalloc: ") + hipGetErrorString(e));
+    h->host = static_cast<int*>(p);
+    h->host_ints = n;
+    void* d = nullptr;
+    HIPCHK(hipHostGetDevicePointer(&d, p, 0));
+    h->host_dev = static_cast<int*>(d);
+    return TPCF_OK;
+}
+
+// Zeroes up to four ranges of ints in one launch.
+tpcf_status clear(tpcf_handle h, std::initializer_list<std::pair<void*, int64_t>> ranges) {
+    ClearRanges r{};
+    int k = 0;
+    for (const auto& x : ranges) {
+        r.p[k] = static_cast<int*>(x.first);
+        r.n[k++] = x.second;
+    }
+    HIPCHK(launch_clear(r, h->stream));
+    return TPCF_OK;
+}
+
+// Waits for the stream and reads n (at most 4) ints of device memory.
+tpcf_status read_flags(tpcf_handle h, const int* d, int n, int* out) {
+    const tpcf_status st = ensure_host(h, 4);
+    if (st != TPCF_OK) return st;
+    HIPCHK(launch_publish(d, n, h->host_dev, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
+    std::copy(h->host, h->host + n, out);
     return TPCF_OK;
 }
 
@@ -207,6 +287,7 @@ void release(tpcf_handle h, DevBuf& b) {
     }
     b.p = nullptr;
     b.bytes = 0;
+    b.held.clear();
 }
 
 template <class T> T* P(DevBuf& b) { return reinterpret_cast<T*>(b.p); }
@@ -580,12 +661,12 @@ tpcf_status build_grid_group(tpcf_handle h, const double* d_pos, const double* d
     if ((st = ensure(h, h->d_catid, sizeof(int) * N)) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_flag, sizeof(int) * 4)) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_catbad, sizeof(int) * h->ncat)) != TPCF_OK) return st;
+    if ((st = ensure_host(h, (size_t)h->ncat + 6)) != TPCF_OK) return st;
     Timer t;
     t_begin(h, 0, t);
-    HIPCHK(launch_fill_i32(P<int>(h->d_count), MS + 1, 0, h->stream));
-    HIPCHK(launch_fill_i32(P<int>(h->d_cursor), MS + 1, 0, h->stream));
-    HIPCHK(launch_fill_i32(P<int>(h->d_flag), 4, 0, h->stream));
-    HIPCHK(launch_fill_i32(P<int>(h->d_catbad), h->ncat, 0, h->stream));
+    if ((st = clear(h, {{h->d_count.p, MS + 1}, {h->d_cursor.p, MS + 1}, {h->d_flag.p, 4}, {h->d_catbad.p, h->ncat}})) !=
+        TPCF_OK)
+        return st;
     HIPCHK(launch_grid_assign(d_pos, d_w, N, P<int64_t>(h->d_pt_off), h->ncat, h->g, P<int>(h->d_cellid),
                               P<int>(h->d_count), P<int>(h->d_flag), P<int>(h->d_catbad), h->stream));
     HIPCHK(launch_grid_scan(P<int>(h->d_count), MS, slab, P<int>(h->d_scanw), h->stream));
@@ -598,17 +679,17 @@ tpcf_status build_grid_group(tpcf_handle h, const double* d_pos, const double* d
     const int64_t nitems_max = M + N / kItemPrims + 1;
     if ((st = ensure(h, h->d_istart, sizeof(int) * (M + 1))) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_icell, sizeof(int) * nitems_max)) != TPCF_OK) return st;
-    if ((st = ensure(h, h->d_icat, sizeof(int) * (h->ncat + 1))) != TPCF_OK) return st;
     HIPCHK(launch_items_count(P<int>(h->d_start), M, P<int>(h->d_cursor), h->stream));
     HIPCHK(launch_grid_scan(P<int>(h->d_cursor), M, P<int>(h->d_istart), P<int>(h->d_scanw), h->stream));
     HIPCHK(launch_grid_fill(d_pos, d_w, N, P<int>(h->d_orig), P<int>(h->d_cellid), h->g, P<float4>(h->d_pf),
                             P<float>(h->d_pw), P<float4>(h->d_pa), P<double4>(h->d_pd), P<int>(h->d_perm), P<int>(h->d_catid),
                             P<int>(h->d_start), P<int>(h->d_istart), P<int>(h->d_icell), h->stream));
-    HIPCHK(launch_items_cat(P<int>(h->d_istart), h->ncat, h->g.ncell, P<int>(h->d_icat), h->stream));
+    HIPCHK(launch_items_cat(P<int>(h->d_istart), h->ncat, h->g.ncell, P<int>(h->d_flag), h->host_dev + 4, h->stream));
     t_end(h, t);
-    h->item_cat.assign(h->ncat + 1, 0);
-    HIPCHK(hipMemcpyAsync(h->item_cat.data(), P<int>(h->d_icat), sizeof(int) * (h->ncat + 1),
-                          hipMemcpyDeviceToHost, h->stream));
+    // the caller's positions and weights have been read when this returns
+    HIPCHK(hipStreamSynchronize(h->stream));
+    h->nonfinite = h->host[4];
+    h->item_cat.assign(h->host + 5, h->host + 6 + h->ncat);
     return TPCF_OK;
 }
 
@@ -781,8 +862,6 @@ tpcf_status plan_chunks(tpcf_handle h) {
 // regions overflowed, harmonics. Nothing is read back: a list that ran out of
 // room raises the flag that pair_pass reads after the last chunk.
 tpcf_status pair_chunk(tpcf_handle h, const Chunk& ch) {
-    HIPCHK(launch_fill_u64(P<unsigned long long>(h->d_lcursor), kSlots * 16, 0ull, h->stream));
-    HIPCHK(launch_fill_i32(P<int>(h->d_flag) + 2, 1, 0, h->stream));  // fix-up list length
     BinArgs b{};
     b.pf = P<float4>(h->d_pf);
     b.pd = P<double4>(h->d_pd);
@@ -1014,10 +1093,8 @@ tpcf_status finalize_group(tpcf_handle h, int32_t n_mult, const int32_t* mult, d
 }
 
 tpcf_status check_nonfinite(tpcf_handle h) {
-    int flag = 0;
-    HIPCHK(hipMemcpyAsync(&flag, P<int>(h->d_flag), sizeof(int), hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(hipStreamSynchronize(h->stream));
-    if (flag) return fail(h, TPCF_ERR_DEVICE, std::to_string(flag) + " non-finite input position(s)");
+    if (h->nonfinite)
+        return fail(h, TPCF_ERR_DEVICE, std::to_string(h->nonfinite) + " non-finite input position(s)");
     return TPCF_OK;
 }
 
@@ -1029,14 +1106,18 @@ tpcf_status check_nonfinite(tpcf_handle h) {
 tpcf_status pair_pass(tpcf_handle h, bool contract_now) {
     tpcf_status st;
     for (int attempt = 0;; ++attempt) {
-        HIPCHK(launch_fill_i32(P<int>(h->d_flag) + 1, 3, 0, h->stream));  // overflow, fix-up length and total
         for (const Chunk& ch : h->chunks) {
+            // flags: overflow and the total of the fix-ups (with the first
+            // chunk), and the length of the chunk's fix-up list between them
+            const bool first = &ch == &h->chunks[0];
+            if ((st = clear(h, {{h->d_lcursor.p, 2 * kSlots * 16}, {P<int>(h->d_flag) + (first ? 1 : 2), first ? 3 : 1}})) !=
+                TPCF_OK)
+                return st;
             if ((st = pair_chunk(h, ch)) != TPCF_OK) return st;
             if (contract_now && (st = contract_chunk(h, ch)) != TPCF_OK) return st;
         }
         int flag[3] = {0, 0, 0};
-        HIPCHK(hipMemcpyAsync(flag, P<int>(h->d_flag) + 1, sizeof(flag), hipMemcpyDeviceToHost, h->stream));
-        HIPCHK(hipStreamSynchronize(h->stream));
+        if ((st = read_flags(h, P<int>(h->d_flag) + 1, 3, flag)) != TPCF_OK) return st;
         h->nfix_total += flag[2];
         if (!flag[0]) return TPCF_OK;
         const unsigned long long ncap = std::min<unsigned long long>(16000000000ull, h->list_cap * 2);
@@ -1260,13 +1341,14 @@ void tpcf_destroy(tpcf_handle h) {
     DevBuf* all[] = {&h->d_e2, &h->d_e2f, &h->d_guard, &h->d_runs, &h->d_shift_f, &h->d_goff,
                      &h->d_vol, &h->d_scale, &h->d_sign_scale, &h->d_gaunt, &h->d_pt_off, &h->d_cellid,
                      &h->d_count, &h->d_start, &h->d_slab, &h->d_cursor, &h->d_tmp, &h->d_tmpz, &h->d_orig, &h->d_pf, &h->d_pw,
-                     &h->d_pa, &h->d_istart, &h->d_icell, &h->d_icat, &h->d_scanw, &h->d_catbad, &h->d_pd, &h->d_perm, &h->d_catid, &h->d_flag, &h->d_list, &h->d_fix, &h->d_lcursor, &h->d_boff,
+                     &h->d_pa, &h->d_istart, &h->d_icell, &h->d_scanw, &h->d_catbad, &h->d_pd, &h->d_perm, &h->d_catid, &h->d_flag, &h->d_list, &h->d_fix, &h->d_lcursor, &h->d_boff,
                      &h->d_cnt, &h->d_A, &h->d_subs, &h->d_catsub, &h->d_part, &h->d_pself, &h->d_G,
                      &h->d_S, &h->d_nd, &h->d_mult, &h->d_coefG, &h->d_coefS, &h->d_lflag,
                      &h->d_xiq, &h->d_xicoef, &h->d_xirr, &h->d_xiruns, &h->d_covx, &h->d_covoff,
                      &h->d_covflag, &h->d_covpart, &h->d_edgeT, &h->d_egaunt, &h->d_eunits, &h->d_errr,
                      &h->d_ecoef, &h->d_eM, &h->d_erhs, &h->d_ezeta, &h->d_emult};
     for (DevBuf* b : all) release(h, *b);
+    if (h->host) hipHostFree(h->host);
     delete h;
 }
 
@@ -1452,14 +1534,12 @@ tpcf_status tpcf_xi_count(tpcf_handle h, int32_t nmu, int64_t* d_counts) {
     if (xi_lds_bytes(h->nb, nmu, npmax) > 160 * 1024)
         return fail(h, TPCF_ERR_RANGE, "the (r, mu) histogram does not fit the LDS");
     HIPCHK(hipSetDevice(h->device));
-    tpcf_status st = check_nonfinite(h);  // also completes the copy of item_cat
+    tpcf_status st = check_nonfinite(h);
     if (st != TPCF_OK) return st;
     if ((st = upload(h, h->d_xiruns, half.data(), sizeof(StencilRun) * std::max<size_t>(half.size(), 1))) != TPCF_OK)
         return st;
     if ((st = ensure(h, h->d_xiq, sizeof(int) * 8 * 32)) != TPCF_OK) return st;
-    HIPCHK(launch_fill_i32(P<int>(h->d_xiq), 8 * 32, 0, h->stream));
-    HIPCHK(launch_fill_u64(reinterpret_cast<unsigned long long*>(d_counts), (int64_t)h->nb * nmu, 0ull,
-                           h->stream));
+    if ((st = clear(h, {{h->d_xiq.p, 8 * 32}, {d_counts, 2 * (int64_t)h->nb * nmu}})) != TPCF_OK) return st;
     XiArgs a{};
     a.pf = P<float4>(h->d_pf);
     a.pd = P<double4>(h->d_pd);
@@ -1523,10 +1603,11 @@ tpcf_status tpcf_xi_multipoles(tpcf_handle h, int32_t nmu, const int64_t* d_coun
     for (int i = 0; i < n_ell; ++i)
         if (h_ells[i] < 0 || h_ells[i] > 60) return fail(h, TPCF_ERR_ARG, "multipole orders must be in 0 .. 60");
     HIPCHK(hipSetDevice(h->device));
-    // c_lk = (2l+1)/2 times the integral of P_l over mu bin k, by 32-point
-    // Gauss-Legendre quadrature on the bin (exact for the degrees allowed)
+    // c_lk = (2l+1)/2 times the integral of P_l over mu bin k, by
+    // Gauss-Legendre quadrature on the bin, with as many points as the highest
+    // degree takes to be exact (up to 2 points - 1; always 32 took 0.1 ms)
     std::vector<double> gx, gw;
-    gauss_legendre(32, gx, gw);
+    gauss_legendre(*std::max_element(h_ells, h_ells + n_ell) / 2 + 1, gx, gw);
     std::vector<double> coef((size_t)n_ell * nmu);
     for (int i = 0; i < n_ell; ++i) {
         const int l = h_ells[i];
@@ -1646,13 +1727,12 @@ tpcf_status tpcf_precision_matrix(tpcf_handle h, int32_t n_d, const double* d_co
     HIPCHK(hipSetDevice(h->device));
     tpcf_status st;
     if ((st = ensure(h, h->d_covflag, sizeof(int))) != TPCF_OK) return st;
-    HIPCHK(launch_fill_i32(P<int>(h->d_covflag), 1, 0, h->stream));
+    if ((st = clear(h, {{h->d_covflag.p, 1}})) != TPCF_OK) return st;
     const double hartlap = (n_mocks - n_d - 2.0) / (n_mocks - 1.0);
     if ((st = ensure(h, h->d_covpart, sizeof(double) * (size_t)n_d * n_d)) != TPCF_OK) return st;
     HIPCHK(launch_cov_invert(d_cov, d_prec, P<double>(h->d_covpart), n_d, hartlap, P<int>(h->d_covflag), h->stream));
     int bad = 0;
-    HIPCHK(hipMemcpyAsync(&bad, h->d_covflag.p, sizeof(int), hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(hipStreamSynchronize(h->stream));
+    if ((st = read_flags(h, P<int>(h->d_covflag), 1, &bad)) != TPCF_OK) return st;
     if (bad) return fail(h, TPCF_ERR_RANGE, "the covariance is not positive definite");
     return TPCF_OK;
 }
@@ -1894,11 +1974,10 @@ tpcf_status tpcf_edge_correct_isotropic(tpcf_handle h, int32_t n_ell, const doub
     tpcf_status st;
     if ((st = upload(h, h->d_edgeT, T.data(), sizeof(double) * T.size())) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_covflag, sizeof(int))) != TPCF_OK) return st;
-    HIPCHK(launch_fill_i32(P<int>(h->d_covflag), 1, 0, h->stream));
+    if ((st = clear(h, {{h->d_covflag.p, 1}})) != TPCF_OK) return st;
     HIPCHK(launch_edge_iso(d_N, d_R, P<double>(h->d_edgeT), nl, h->nb * h->nb, d_out, P<int>(h->d_covflag), h->stream));
     int bad = 0;
-    HIPCHK(hipMemcpyAsync(&bad, h->d_covflag.p, sizeof(int), hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(hipStreamSynchronize(h->stream));
+    if ((st = read_flags(h, P<int>(h->d_covflag), 1, &bad)) != TPCF_OK) return st;
     if (bad) return fail(h, TPCF_ERR_RANGE, "singular coupling matrix (random multipoles)");
     return TPCF_OK;
 }
@@ -1958,8 +2037,7 @@ tpcf_status tpcf_edge_correct(tpcf_handle h, const double* d_nnn_N, int64_t n_da
     if ((st = ensure(h, h->d_erhs, sizeof(double) * (size_t)nsys * n)) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_ezeta, sizeof(double) * (size_t)nz)) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_covflag, sizeof(int))) != TPCF_OK) return st;
-    HIPCHK(launch_fill_i32(P<int>(h->d_covflag), 1, 0, h->stream));
-    HIPCHK(launch_fill_u64(P<unsigned long long>(h->d_ezeta), nz, 0ull, h->stream));
+    if ((st = clear(h, {{h->d_covflag.p, 1}, {h->d_ezeta.p, 2 * nz}})) != TPCF_OK) return st;
     EdgeArgs a{};
     a.N = d_nnn_N;
     a.R = d_nnn_R;
@@ -1985,8 +2063,7 @@ tpcf_status tpcf_edge_correct(tpcf_handle h, const double* d_nnn_N, int64_t n_da
     if (d_zeta)
         HIPCHK(hipMemcpyAsync(d_zeta, h->d_ezeta.p, sizeof(double) * (size_t)nz, hipMemcpyDeviceToDevice, h->stream));
     int bad = 0;
-    HIPCHK(hipMemcpyAsync(&bad, h->d_covflag.p, sizeof(int), hipMemcpyDeviceToHost, h->stream));
-    HIPCHK(hipStreamSynchronize(h->stream));
+    if ((st = read_flags(h, P<int>(h->d_covflag), 1, &bad)) != TPCF_OK) return st;
     if (bad) return fail(h, TPCF_ERR_RANGE, "singular coupling matrix (random triplet counts)");
     return TPCF_OK;
 }

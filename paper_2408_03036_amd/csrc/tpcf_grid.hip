@@ -231,9 +231,22 @@ __global__ void k_grid_fill(const double* __restrict__ pos, const double* __rest
     if (at % kItemPrims == 0) item_cell[item_start[id] + at / kItemPrims] = id;
 }
 
-__global__ void k_fill_i32(int* p, int64_t n, int v) {
+// Zeroes several buffers in one launch (a launch of its own costs each small
+// one 3 us of a call that takes 200).
+__global__ void k_clear(ClearRanges r) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
+#pragma unroll
+    for (int k = 0; k < kClearRanges; ++k) {
+        if (i >= 0 && i < r.n[k]) r.p[k][i] = 0;
+        i -= r.n[k];
+    }
+}
+// A small table, out of the launch's own arguments.
+__global__ void k_put(uint32_t* __restrict__ dst, int n, PutWords w) {
+    for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = w.v[i];
+}
+__global__ void k_publish(const int* __restrict__ src, int n, int* __restrict__ host) {
+    if ((int)threadIdx.x < n) host[threadIdx.x] = src[threadIdx.x];
 }
 __global__ void k_fill_u64(unsigned long long* p, int64_t n, unsigned long long v) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -253,9 +266,13 @@ __global__ void k_items_count(const int* __restrict__ cell_start, int64_t m, int
     nitems[c] = (n + kItemPrims - 1) / kItemPrims;
 }
 
-__global__ void k_items_cat(const int* __restrict__ item_start, int ncat, int ncell, int* __restrict__ item_cat) {
+// What the host reads of a grid, written to its (pinned) memory: the count of
+// non-finite positions, and the first work item of every catalogue.
+__global__ void k_items_cat(const int* __restrict__ item_start, int ncat, int ncell,
+                            const int* __restrict__ nonfinite, int* __restrict__ host) {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c <= ncat) item_cat[c] = item_start[(int64_t)c * ncell];
+    if (c == 0) host[0] = *nonfinite;
+    if (c <= ncat) host[1 + c] = item_start[(int64_t)c * ncell];
 }
 
 inline unsigned nblk(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
@@ -268,9 +285,10 @@ hipError_t launch_items_count(const int* cell_start, int64_t m, int* nitems, hip
     return hipGetLastError();
 }
 
-hipError_t launch_items_cat(const int* item_start, int ncat, int ncell, int* item_cat, hipStream_t s) {
+hipError_t launch_items_cat(const int* item_start, int ncat, int ncell, const int* nonfinite, int* host,
+                            hipStream_t s) {
     hipLaunchKernelGGL(k_items_cat, dim3(nblk(ncat + 1, 256)), dim3(256), 0, s, item_start, ncat, ncell,
-                       item_cat);
+                       nonfinite, host);
     return hipGetLastError();
 }
 
@@ -329,9 +347,22 @@ hipError_t launch_grid_fill(const double* pos, const double* w, int64_t n, const
     return hipGetLastError();
 }
 
-hipError_t launch_fill_i32(int* p, int64_t n, int v, hipStream_t s) {
+hipError_t launch_clear(const ClearRanges& r, hipStream_t s) {
+    int64_t n = 0;
+    for (int k = 0; k < kClearRanges; ++k) n += r.n[k];
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_fill_i32, dim3(nblk(n, 256)), dim3(256), 0, s, p, n, v);
+    hipLaunchKernelGGL(k_clear, dim3(nblk(n, 256)), dim3(256), 0, s, r);
+    return hipGetLastError();
+}
+
+hipError_t launch_put(uint32_t* dst, int n, const PutWords& w, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_put, dim3(1), dim3(256), 0, s, dst, n, w);
+    return hipGetLastError();
+}
+
+hipError_t launch_publish(const int* src, int n, int* host, hipStream_t s) {
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, src, n, host);
     return hipGetLastError();
 }
 

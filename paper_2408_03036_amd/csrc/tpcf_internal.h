@@ -68,12 +68,24 @@ hipError_t launch_grid_fill(const double* pos, const double* w, int64_t n, const
                             const int* cellid, Grid g, float4* pf, float* pw, float4* pa, double4* pd,
                             int* perm, int* catid, const int* cell_start, const int* item_start, int* item_cell,
                             hipStream_t s);
-hipError_t launch_fill_i32(int* p, int64_t n, int v, hipStream_t s);
+constexpr int kClearRanges = 4;
+struct ClearRanges {
+    int* p[kClearRanges];
+    int64_t n[kClearRanges];  // ints
+};
+hipError_t launch_clear(const ClearRanges& r, hipStream_t s);
+constexpr int kPutWords = 768;  // 3 KB, within the 4 KB of a launch's arguments
+struct PutWords {
+    uint32_t v[kPutWords];
+};
+hipError_t launch_put(uint32_t* dst, int n, const PutWords& w, hipStream_t s);
+hipError_t launch_publish(const int* src, int n, int* host, hipStream_t s);  // n <= 64
 // Work items of the binning pass: each cell's primaries in blocks of kItemPrims
 // (launch_grid_fill writes the cell of each item).
 constexpr int kItemPrims = 16;
 hipError_t launch_items_count(const int* cell_start, int64_t m, int* nitems, hipStream_t s);
-hipError_t launch_items_cat(const int* item_start, int ncat, int ncell, int* item_cat, hipStream_t s);
+hipError_t launch_items_cat(const int* item_start, int ncat, int ncell, const int* nonfinite, int* host,
+                            hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long* p, int64_t n, unsigned long long v, hipStream_t s);
 
 // Pair pass (tpcf_pairs.hip)

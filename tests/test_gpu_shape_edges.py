@@ -321,3 +321,59 @@ def test_parts_list_lengths(torch, prec, lmax, weighted):
     mask = np.tril(np.ones((lmax + 1, lmax + 1), dtype=bool))
     off = np.abs(alm[..., mask] - ref[..., mask]).max() / np.abs(ref).max()
     assert off <= (1e-12 if prec == T.PREC_FP64 else 1e-5), off
+
+
+def test_tables_between_calls(torch):
+    """Calls of one handle whose tables (catalogue offsets, multipoles, vector
+    entries) are new, repeated, changed at the same size, one launch's size,
+    several launches' and beyond: each result is a fresh handle's."""
+    rng = np.random.default_rng(31)
+    edges = np.linspace(0.0, 30.0, 5)
+    few = [(0, 0, 0), (1, 1, 2), (2, 0, 2)]
+    many = [(a, b, L) for a in range(5) for b in range(5) for L in range(abs(a - b), a + b + 1, 2)]  # 20 KB of weights
+    cats = {k: torch.from_numpy(rng.uniform(0.0, 100.0, (n, 3))).cuda() for k, n in (("a", 700), ("b", 700), ("c", 1900))}
+    sizes = {"a": [700], "b": [300, 400], "c": [1900]}
+
+    def run(h, k, mults):
+        return h.run_catalogs(sizes[k], sizes[k], cats[k], None, mults).cpu().numpy()
+
+    h = T.Handle(100.0, edges, 4)
+    for k, mults in (("a", few), ("a", few), ("b", few), ("a", few[::-1]), ("c", many), ("a", many), ("a", few)):
+        say(f"  tables: catalogue {k}, {len(mults)} multipoles")
+        f = T.Handle(100.0, edges, 4)
+        assert np.array_equal(run(h, k, mults), run(f, k, mults))
+        f.close()
+    src = torch.from_numpy(rng.standard_normal((40, 2000))).cuda()
+    for n in (3, 384, 385, 1536, 1537, 385):  # 3 KB a launch, 12 KB in four
+        off = rng.permutation(2000)[:n].astype(np.int64)
+        say(f"  tables: {n} entries")
+        f = T.Handle(100.0, edges, 0)
+        for x, y in zip(h.covariance(src, offsets=off), f.covariance(src, offsets=off)):
+            assert np.array_equal(x.cpu().numpy(), y.cpu().numpy())
+        f.close()
+    h.close()
+
+
+# an even and an odd number of quadrature points, the fewest and the most
+@pytest.mark.parametrize("ells", [[0], [1, 0], [2, 3], [60, 59, 0, 31]])
+def test_xi_multipole_orders(torch, ells):
+    """xi_l from given counts against Legendre integrals over the bins in
+    closed form. A weight is a sum of values of degree up to l + 1 by
+    recurrences, each within (l + 4) ulps; both sides have one."""
+    from numpy.polynomial import legendre
+    rng = np.random.default_rng(37)
+    nb, nmu, n, box = 3, 40, 5000, 200.0
+    edges = np.linspace(10.0, 40.0, nb + 1)
+    dd = rng.integers(0, 9000, (nb, nmu))
+    h = T.Handle(box, edges, 0)
+    say(f"  xi multipoles: {ells}")
+    got = h.xi_multipoles(torch.from_numpy(dd).cuda(), n, ells).cpu().numpy()
+    h.close()
+    vol = 4.0 * np.pi / 3.0 * np.diff(edges**3)
+    x = dd / (n * (n - 1.0) * vol / (nmu * box**3))[:, None] - 1.0
+    e = -1.0 + 2.0 * np.arange(nmu + 1) / nmu
+    for i, l in enumerate(ells):
+        p = [legendre.legval(e, np.eye(l + 2)[k]) for k in (l + 1, max(l - 1, 0))]
+        c = 0.5 * np.diff(p[0] - p[1] if l else e)  # (2l+1)/2 of the integral of P_l
+        tol = 2.0 * (2 * l + 1) * (l + 4) * 2.0**-52 * nmu * np.abs(x).max()
+        assert np.abs(got[i] - x @ c).max() <= tol, (l, np.abs(got[i] - x @ c).max(), tol)
