@@ -645,6 +645,7 @@ tpcf_status build_grid_group(tpcf_handle h, const double* d_pos, const double* d
     if ((st = ensure(h, h->d_cellid, sizeof(int) * N)) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_count, sizeof(int) * (MS + 1))) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_start, sizeof(int) * (M + 1))) != TPCF_OK) return st;
+    if ((st = ensure(h, h->d_istart, sizeof(int) * (M + 1))) != TPCF_OK) return st;
     if (MS > M && (st = ensure(h, h->d_slab, sizeof(int) * (MS + 1))) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_scanw, sizeof(int) * grid_scan_work_ints(MS))) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_cursor, sizeof(int) * (MS + 1))) != TPCF_OK) return st;
@@ -669,7 +670,9 @@ tpcf_status build_grid_group(tpcf_handle h, const double* d_pos, const double* d
         return st;
     HIPCHK(launch_grid_assign(d_pos, d_w, N, P<int64_t>(h->d_pt_off), h->ncat, h->g, P<int>(h->d_cellid),
                               P<int>(h->d_count), P<int>(h->d_flag), P<int>(h->d_catbad), h->stream));
-    HIPCHK(launch_grid_scan(P<int>(h->d_count), MS, slab, P<int>(h->d_scanw), h->stream));
+    // a cell's count gives its work items too, a slab's does not
+    HIPCHK(launch_grid_scan(P<int>(h->d_count), MS, slab, MS > M ? nullptr : P<int>(h->d_istart), P<int>(h->d_scanw),
+                            h->stream));
     if (MS > M) HIPCHK(launch_grid_cells(slab, M, h->g.zsub, P<int>(h->d_start), h->stream));
     HIPCHK(launch_grid_scatter(P<int>(h->d_cellid), N, h->g, slab, P<int>(h->d_cursor), d_pos, P<int>(h->d_tmp),
                                P<double>(h->d_tmpz), h->stream));
@@ -677,10 +680,11 @@ tpcf_status build_grid_group(tpcf_handle h, const double* d_pos, const double* d
                              P<int>(h->d_orig), h->stream));
     // work items of the binning pass: blocks of up to kItemPrims primaries of one cell
     const int64_t nitems_max = M + N / kItemPrims + 1;
-    if ((st = ensure(h, h->d_istart, sizeof(int) * (M + 1))) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_icell, sizeof(int) * nitems_max)) != TPCF_OK) return st;
-    HIPCHK(launch_items_count(P<int>(h->d_start), M, P<int>(h->d_cursor), h->stream));
-    HIPCHK(launch_grid_scan(P<int>(h->d_cursor), M, P<int>(h->d_istart), P<int>(h->d_scanw), h->stream));
+    if (MS > M) {
+        HIPCHK(launch_items_count(P<int>(h->d_start), M, P<int>(h->d_cursor), h->stream));
+        HIPCHK(launch_grid_scan(P<int>(h->d_cursor), M, P<int>(h->d_istart), nullptr, P<int>(h->d_scanw), h->stream));
+    }
     HIPCHK(launch_grid_fill(d_pos, d_w, N, P<int>(h->d_orig), P<int>(h->d_cellid), h->g, P<float4>(h->d_pf),
                             P<float>(h->d_pw), P<float4>(h->d_pa), P<double4>(h->d_pd), P<int>(h->d_perm), P<int>(h->d_catid),
                             P<int>(h->d_start), P<int>(h->d_istart), P<int>(h->d_icell), h->stream));
@@ -1020,10 +1024,16 @@ tpcf_status reduce_group(tpcf_handle h) {
     if ((st = ensure(h, h->d_S, sizeof(double) * h->ncat * sw)) != TPCF_OK) return st;
     Timer t;
     t_begin(h, 3, t);
-    HIPCHK(launch_reduce_partials(nullptr, P<double>(h->d_part), h->gsize,
-                                  P<int>(h->d_catsub), h->ncat, P<double>(h->d_G), h->stream));
-    HIPCHK(launch_reduce_partials(nullptr, P<double>(h->d_pself), sw, P<int>(h->d_catsub), h->ncat,
-                                  P<double>(h->d_S), h->stream));
+    ReduceArgs a{};
+    a.part[0] = P<double>(h->d_part);
+    a.part[1] = P<double>(h->d_pself);
+    a.out[0] = P<double>(h->d_G);
+    a.out[1] = P<double>(h->d_S);
+    a.width[0] = h->gsize;
+    a.width[1] = sw;
+    a.cat_sub = P<int>(h->d_catsub);
+    a.ncat = h->ncat;
+    HIPCHK(launch_reduce_partials(a, h->stream));
     t_end(h, t);
     return TPCF_OK;
 }

@@ -936,16 +936,28 @@ __global__ void __launch_bounds__(256) k_self_moments(SelfArgs a) {
     }
 }
 
-__global__ void k_reduce_partials(const float* __restrict__ p32, const double* __restrict__ p64,
-                                  int64_t width, const int* __restrict__ cat_sub, int ncat,
-                                  double* __restrict__ out) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Sums of each catalogue's subchunks, those of the contraction and of the self
+// moments in one launch. Latency bound: a thread adds one value of a few dozen
+// subchunks in their order, eight loads in flight.
+__global__ void k_reduce_partials(ReduceArgs a) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int c = blockIdx.y;
-    if (e >= width || c >= ncat) return;
+    if (i >= a.width[0] + a.width[1]) return;
+    const int k = i >= a.width[0];
+    const int64_t width = a.width[k], e = k ? i - a.width[0] : i;
+    const double* p = a.part[k] + e;
+    const int q1 = a.cat_sub[c + 1];
     double s = 0.0;
-    for (int q = cat_sub[c]; q < cat_sub[c + 1]; ++q)
-        s += p32 ? (double)p32[(int64_t)q * width + e] : p64[(int64_t)q * width + e];
-    out[(int64_t)c * width + e] = s;
+    int q = a.cat_sub[c];
+    for (; q + 8 <= q1; q += 8) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = p[(q + u) * width];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    for (; q < q1; ++q) s += p[q * width];
+    a.out[k][c * width + e] = s;
 }
 
 __global__ void k_finalize(FinalArgs a) {
@@ -1245,11 +1257,10 @@ hipError_t launch_self_moments(const SelfArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_reduce_partials(const float* p32, const double* p64, int64_t width,
-                                  const int* cat_sub, int ncat, double* out, hipStream_t s) {
-    if (ncat <= 0 || width <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_reduce_partials, dim3((unsigned)((width + 255) / 256), ncat), dim3(256), 0,
-                       s, p32, p64, width, cat_sub, ncat, out);
+hipError_t launch_reduce_partials(const ReduceArgs& a, hipStream_t s) {
+    const int64_t n = a.width[0] + a.width[1];
+    if (a.ncat <= 0 || n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_reduce_partials, dim3((unsigned)((n + 255) / 256), a.ncat), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -11,7 +11,7 @@
 // points at a time. With one counter and one quadratic rank per cell, 102,051
 // points in one cell took 14.1 ms (order 11.8 ms, the two passes of atomics on
 // the one counter 1.15 ms each); with slabs the three kernels take 0.026 ms.
-#include "tpcf_internal.h"
+#include "tpcf_cells.h"
 
 namespace tpcf {
 
@@ -70,84 +70,134 @@ __global__ void k_grid_assign(const double* __restrict__ pos, int64_t n,
     atomicAdd(&count[(int64_t)id * g.zsub + slab_of(z, cz, g)], 1);
 }
 
-// Single-workgroup exclusive scan: each thread scans a contiguous segment.
-__global__ void __launch_bounds__(1024) k_grid_scan(const int* __restrict__ count, int64_t m,
-                                                    int* __restrict__ start) {
-    __shared__ int part[1024];
-    const int t = threadIdx.x;
-    const int64_t seg = (m + 1023) / 1024;
-    const int64_t a = t * seg;
-    const int64_t b = a + seg < m ? a + seg : m;
-    int s = 0;
-    for (int64_t i = a; i < b; ++i) s += count[i];
-    part[t] = s;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        int v = t >= off ? part[t - off] : 0;
-        __syncthreads();
-        part[t] += v;
-        __syncthreads();
-    }
-    int run = part[t] - s;
-    for (int64_t i = a; i < b; ++i) {
-        start[i] = run;
-        run += count[i];
-    }
-    if (t == 1023) start[m] = part[1023];
+// Exclusive scan of m counts, and of the work items that cells of those counts
+// hold, both in one 64-bit sum (counts in the low half: all of them are less
+// than 2^31). Blocks of kScanBlock elements: their sums, then each block's scan
+// from the sum of the blocks before it, which a block adds up itself: up to
+// kScanDirect of them that costs less than a launch for their scan.
+// One block takes k_scan_apply alone. Launches bound this stage on small
+// grids: with a scan of its own for the items, and a launch for the offsets,
+// 41,000 cells took seven launches and 35 us of kernels, now two and 7.5.
+constexpr int kScanBlock = 4096;  // 256 threads x 16 elements
+constexpr int kScanDirect = 2048;
+
+using ScanSum = unsigned long long;
+
+__device__ __forceinline__ ScanSum scan_value(int n) {
+    return (ScanSum)(uint32_t)n | ((ScanSum)(uint32_t)((n + kItemPrims - 1) / kItemPrims) << 32);
 }
 
-// Three-phase exclusive scan of m counts: per-block sums of kScanBlock
-// elements, a scan of the block sums (k_grid_scan), then each block's scan
-// plus its offset.
-constexpr int kScanBlock = 4096;  // 256 threads x 16 elements
+// Elements [e0, e0 + 16) of the counts (zero past m).
+__device__ __forceinline__ void scan_load(const int* __restrict__ count, int64_t e0, int64_t m, int (&v)[16]) {
+    if (e0 + 16 <= m) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int4 q = *reinterpret_cast<const int4*>(count + e0 + 4 * k);
+            v[4 * k] = q.x, v[4 * k + 1] = q.y, v[4 * k + 2] = q.z, v[4 * k + 3] = q.w;
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = e0 + k < m ? count[e0 + k] : 0;
+    }
+}
+
+__device__ __forceinline__ ScanSum wave_sum(ScanSum v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    return v;
+}
+
+__device__ __forceinline__ ScanSum wave_scan(ScanSum v) {
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const ScanSum u = __shfl_up(v, o);
+        if (lane_id() >= o) v += u;
+    }
+    return v;
+}
 
 __global__ void __launch_bounds__(256) k_scan_sums(const int* __restrict__ count, int64_t m,
-                                                   int* __restrict__ sums) {
-    __shared__ int red[256];
-    const int64_t b0 = (int64_t)blockIdx.x * kScanBlock;
-    int s = 0;
-    for (int i = threadIdx.x; i < kScanBlock; i += 256) {
-        const int64_t e = b0 + i;
-        if (e < m) s += count[e];
-    }
-    red[threadIdx.x] = s;
+                                                   ScanSum* __restrict__ sums) {
+    __shared__ ScanSum part[4];
+    int v[16];
+    scan_load(count, (int64_t)blockIdx.x * kScanBlock + 16 * threadIdx.x, m, v);
+    ScanSum s = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) s += scan_value(v[k]);
+    s = wave_sum(s);
+    if (lane_id() == 0) part[threadIdx.x >> 6] = s;
     __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) sums[blockIdx.x] = red[0];
+    if (threadIdx.x == 0) sums[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
 }
 
-__global__ void __launch_bounds__(256) k_scan_apply(const int* __restrict__ count, int64_t m,
-                                                    const int* __restrict__ boff, int* __restrict__ start) {
-    __shared__ int part[256];
-    const int64_t b0 = (int64_t)blockIdx.x * kScanBlock;
+// One workgroup, a segment of the sums per thread.
+__global__ void __launch_bounds__(1024) k_scan_offsets(const ScanSum* __restrict__ sums, int64_t nb,
+                                                       ScanSum* __restrict__ offs) {
+    __shared__ ScanSum part[16];
     const int t = threadIdx.x;
-    // thread t owns elements [b0 + 16 t, b0 + 16 t + 16)
-    int v[16];
-    int s = 0;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int64_t e = b0 + 16 * t + k;
-        v[k] = e < m ? count[e] : 0;
-        s += v[k];
-    }
-    part[t] = s;
+    const int64_t seg = (nb + 1023) / 1024;
+    const int64_t a = t * seg < nb ? t * seg : nb;
+    const int64_t b = a + seg < nb ? a + seg : nb;
+    ScanSum s = 0;
+    for (int64_t i = a; i < b; ++i) s += sums[i];
+    const ScanSum incl = wave_scan(s);
+    if (lane_id() == 63) part[t >> 6] = incl;
     __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-        const int x = t >= o ? part[t - o] : 0;
-        __syncthreads();
-        part[t] += x;
-        __syncthreads();
+    ScanSum run = incl - s;
+    for (int w = 0; w < t >> 6; ++w) run += part[w];
+    for (int64_t i = a; i < b; ++i) {
+        offs[i] = run;
+        run += sums[i];
     }
-    int run = boff[blockIdx.x] + part[t] - s;
+}
+
+// The offset of a block: offs, or with none the sums of the blocks before it.
+__global__ void __launch_bounds__(256) k_scan_apply(const int* __restrict__ count, int64_t m,
+                                                    const ScanSum* __restrict__ sums,
+                                                    const ScanSum* __restrict__ offs, int* __restrict__ start,
+                                                    int* __restrict__ istart) {
+    __shared__ ScanSum part[4], pre[4];
+    const int t = threadIdx.x, wave = t >> 6;
+    const int64_t e0 = (int64_t)blockIdx.x * kScanBlock + 16 * t;
+    int v[16];
+    scan_load(count, e0, m, v);
+    ScanSum s = 0, before = 0;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int64_t e = b0 + 16 * t + k;
-        if (e < m) start[e] = run;
-        if (e == m - 1) start[m] = run + v[k];
-        run += v[k];
+    for (int k = 0; k < 16; ++k) s += scan_value(v[k]);
+    if (offs == nullptr)
+        for (int i = t; i < (int)blockIdx.x; i += 256) before += sums[i];
+    else if (t == 0)
+        before = offs[blockIdx.x];
+    before = wave_sum(before);
+    const ScanSum incl = wave_scan(s);
+    if (lane_id() == 63) {
+        part[wave] = incl;
+        pre[wave] = before;
+    }
+    __syncthreads();
+    ScanSum run = pre[0] + pre[1] + pre[2] + pre[3] + incl - s;
+    for (int w = 0; w < wave; ++w) run += part[w];
+    int o[17], q[17];
+#pragma unroll
+    for (int k = 0; k < 17; ++k) {
+        o[k] = (int)(uint32_t)run;
+        q[k] = (int)(uint32_t)(run >> 32);
+        if (k < 16) run += scan_value(v[k]);
+    }
+    if (e0 + 16 <= m) {
+#pragma unroll
+        for (int k = 0; k < 16; k += 4) {
+            *reinterpret_cast<int4*>(start + e0 + k) = make_int4(o[k], o[k + 1], o[k + 2], o[k + 3]);
+            if (istart) *reinterpret_cast<int4*>(istart + e0 + k) = make_int4(q[k], q[k + 1], q[k + 2], q[k + 3]);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 17; ++k) {
+        // the ragged end, and the total past the last element
+        if (e0 + 16 <= m ? k == 16 && e0 + 16 == m : e0 + k <= m && (k > 0 || e0 < m)) {
+            start[e0 + k] = o[k];
+            if (istart) istart[e0 + k] = q[k];
+        }
     }
 }
 
@@ -301,20 +351,17 @@ hipError_t launch_grid_assign(const double* pos, const double*, int64_t n, const
     return hipGetLastError();
 }
 
-hipError_t launch_grid_scan(const int* count, int64_t m, int* start, int* work, hipStream_t s) {
+hipError_t launch_grid_scan(const int* count, int64_t m, int* start, int* istart, int* work, hipStream_t s) {
     const int64_t nb = (m + kScanBlock - 1) / kScanBlock;
-    if (nb <= 1) {
-        hipLaunchKernelGGL(k_grid_scan, dim3(1), dim3(1024), 0, s, count, m, start);
-        return hipGetLastError();
-    }
-    // work: nb block sums, then nb + 1 block offsets
-    hipLaunchKernelGGL(k_scan_sums, dim3((unsigned)nb), dim3(256), 0, s, count, m, work);
-    hipLaunchKernelGGL(k_grid_scan, dim3(1), dim3(1024), 0, s, work, nb, work + nb);
-    hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(256), 0, s, count, m, work + nb, start);
+    ScanSum* sums = reinterpret_cast<ScanSum*>(work);
+    ScanSum* offs = nb > kScanDirect ? sums + nb : nullptr;
+    if (nb > 1) hipLaunchKernelGGL(k_scan_sums, dim3((unsigned)nb), dim3(256), 0, s, count, m, sums);
+    if (offs) hipLaunchKernelGGL(k_scan_offsets, dim3(1), dim3(1024), 0, s, sums, nb, offs);
+    hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)nb), dim3(256), 0, s, count, m, sums, offs, start, istart);
     return hipGetLastError();
 }
 
-int64_t grid_scan_work_ints(int64_t m) { return 2 * ((m + kScanBlock - 1) / kScanBlock) + 1; }
+int64_t grid_scan_work_ints(int64_t m) { return 4 * ((m + kScanBlock - 1) / kScanBlock); }
 
 hipError_t launch_grid_scatter(const int* cellid, int64_t n, Grid g, const int* start, int* cursor,
                                const double* pos, int* tmp_idx, double* tmp_key, hipStream_t s) {

@@ -55,8 +55,9 @@ struct CatArrays {
 hipError_t launch_grid_assign(const double* pos, const double* w, int64_t n, const int64_t* pt_off,
                               int ncat, Grid g, int* cellid, int* count, int* nonfinite, int* catbad,
                               hipStream_t s);
-// Exclusive scan of m counts into start[0..m]; work holds grid_scan_work_ints(m) ints.
-hipError_t launch_grid_scan(const int* count, int64_t m, int* start, int* work, hipStream_t s);
+// Exclusive scan of m >= 1 counts into start[0..m], and with istart of the work items
+// of cells of those counts into istart[0..m]; work holds grid_scan_work_ints(m) ints.
+hipError_t launch_grid_scan(const int* count, int64_t m, int* start, int* istart, int* work, hipStream_t s);
 int64_t grid_scan_work_ints(int64_t m);
 hipError_t launch_grid_scatter(const int* cellid, int64_t n, Grid g, const int* start, int* cursor,
                                const double* pos, int* tmp_idx, double* tmp_key, hipStream_t s);
@@ -272,8 +273,14 @@ struct SelfArgs {
 hipError_t launch_self_moments(const SelfArgs& a, hipStream_t s);
 
 // Fixed-order sums of subchunk partials per catalogue.
-hipError_t launch_reduce_partials(const float* p32, const double* p64, int64_t width,
-                                  const int* cat_sub, int ncat, double* out, hipStream_t s);
+struct ReduceArgs {
+    const double* part[2];  // [subchunk][width]: contraction, self moments
+    double* out[2];         // [catalogue][width]
+    int64_t width[2];
+    const int* cat_sub;     // [ncat+1]
+    int ncat;
+};
+hipError_t launch_reduce_partials(const ReduceArgs& a, hipStream_t s);
 
 struct FinalArgs {
     const double* G;         // [ncat][gsize] (FP64, upper-triangle-complete symmetric)

@@ -377,3 +377,27 @@ def test_xi_multipole_orders(torch, ells):
         c = 0.5 * np.diff(p[0] - p[1] if l else e)  # (2l+1)/2 of the integral of P_l
         tol = 2.0 * (2 * l + 1) * (l + 4) * 2.0**-52 * nmu * np.abs(x).max()
         assert np.abs(got[i] - x @ c).max() <= tol, (l, np.abs(got[i] - x @ c).max(), tol)
+
+
+# cells of a catalogue: few, one scan block exactly (16^3) and two of them, a
+# ragged last block, many blocks, and more than add up their own offsets (205^3)
+@pytest.mark.parametrize("nc,ncat", [(7, 1), (16, 1), (16, 2), (17, 3), (64, 1), (100, 1), (205, 1)])
+def test_cell_scan_blocks(torch, nc, ncat):
+    """Pair counts (integers) on grids of nc^3 cells whose scans take one block to
+    thousands: the oracle's."""
+    rng = np.random.default_rng(41)
+    box, n = 100.0, 1200
+    rmax = 3.0 * box / (nc + 0.5)
+    edges = np.array([0.0, 0.4, 1.0]) * rmax
+    cats = []
+    for c in range(ncat):
+        p = rng.uniform(0.0, box, (n // 4, 1, 3))
+        cats.append(np.mod(p + rng.uniform(-0.4, 0.4, (n // 4, 4, 3)) * rmax, box).reshape(-1, 3))
+    cats[0][0] = 0.0
+    cats[0][1] = np.nextafter(box, 0.0)  # the first and the last cell
+    say(f"  scan: {nc}^3 cells, {ncat} catalogues")
+    h = T.Handle(box, edges, 0, grid_refine=3)
+    h.run_catalogs([n] * ncat, [n] * ncat, torch.from_numpy(np.vstack(cats)).cuda(), None, [(0, 0, 0)])
+    pairs = h.pair_count()
+    h.close()
+    assert pairs == sum(O.run(c, box, edges, 0, [(0, 0, 0)])[2].npairs for c in cats)
