@@ -255,6 +255,29 @@ def test_xi_just_outside_the_shells(torch, box, rmin, rmax, nb):
     assert np.array_equal(dd, O.xi_counts(pos, box, edges, nmu))
 
 
+# growing bins, one bin, and bins narrower than the guard bands between wide ones
+@pytest.mark.parametrize("edges", [np.geomspace(2.0, 60.0, 18), [20.0, 50.0],
+                                   [0.0, 10.0, 10.0 + 1e-6, 10.0 + 2e-6, 35.0, 35.0 + 1e-5, 60.0]],
+                         ids=["log", "one", "narrow"])
+@pytest.mark.parametrize("box,refine", [(400.0, 0), (120.0, 0)])
+def test_xi_around_unequal_edges(torch, box, refine, edges):
+    """Half of the points lie at a bin edge from another one, off by 1e-9 to
+    1e-3 of it on either side: every count is the oracle's."""
+    rng = np.random.default_rng(43)
+    n, nmu, edges = 1500, 11, np.asarray(edges)
+    p = rng.uniform(0.0, box, (n, 3))
+    d = rng.standard_normal((n, 3))
+    d /= np.linalg.norm(d, axis=1, keepdims=True)
+    off = 10.0 ** rng.uniform(-9.0, -3.0, n) * rng.choice([-1.0, 1.0], n)
+    pos = np.vstack([p, np.mod(p + d * (rng.choice(edges, n) * (1.0 + off))[:, None], box)])
+    say(f"  xi edges: box={box} nb={len(edges) - 1}")
+    h = T.Handle(box, edges, 0, grid_refine=refine)
+    h.build_grid(torch.from_numpy(pos).cuda(), None, 2 * n)
+    dd = h.xi_count(nmu).cpu().numpy()
+    h.close()
+    assert np.array_equal(dd, O.xi_counts(pos, box, edges, nmu))
+
+
 # cells of r_max / k, and one cell (box = 2 r_max)
 @pytest.mark.parametrize("box,refine", [(400.0, 1), (400.0, 3), (400.0, 4), (120.0, 0)])
 @pytest.mark.parametrize("prec,weighted", [(T.PREC_FP64, False), (T.PREC_FP32, False), (T.PREC_FP32, True)])
