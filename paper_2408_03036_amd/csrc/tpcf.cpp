@@ -112,11 +112,14 @@ struct tpcf_handle_s {
     int64_t chunk_cap = 0;
     double hits_per_list = 0.0;  // predicted mean length of a (p, b) list
     double list_grow = 1.0;      // list room found needed beyond the prediction (doubles per overflow)
+    double chunk_budget = 0.0;   // bytes of a chunk's operand and lists (0: half the workspace)
+    double chunk_bytes = 0.0;    // of the largest chunk planned
+    bool full = false;           // an allocation did not fit
     unsigned long long list_cap = 0;
     DevBuf d_fix;
     int64_t nfix_total = 0;   // primaries rebinned with exact counts (all chunks since creation)
     double inv_vst = 0.0;     // 1 / stencil volume
-    DevBuf d_list, d_lcursor, d_boff, d_cnt, d_A, d_subs, d_catsub, d_part, d_pself, d_G, d_S, d_nd,
+    DevBuf d_list, d_lcursor, d_boff, d_cnt, d_A, d_subs, d_catsub, d_part, d_G, d_S, d_nd,
         d_mult, d_coefG, d_coefS, d_lflag;
     int64_t ldA = 0;
     int stage = 0;         // 0 nothing, 1 grid, 2 a_lm, 3 contracted
@@ -187,12 +190,22 @@ tpcf_status ensure(tpcf_handle h, DevBuf& b, size_t bytes) {
     }
     if (bytes == 0) bytes = 256;
     bytes = (bytes + 255) / 256 * 256;
-    if (h->used + (int64_t)bytes > h->limit)
+    // the buffer of partial sums holds nothing between two contractions
+    if (h->used + (int64_t)bytes > h->limit && &b != &h->d_part && h->d_part.p) {
+        hipFree(h->d_part.p);
+        h->used -= (int64_t)h->d_part.bytes;
+        h->d_part = DevBuf{};
+    }
+    if (h->used + (int64_t)bytes > h->limit) {
+        h->full = true;
         return fail(h, TPCF_ERR_ALLOC, "workspace limit exceeded (" + std::to_string(h->used + bytes) +
                                            " > " + std::to_string(h->limit) + " bytes)");
+    }
     hipError_t e = hipMalloc(&b.p, bytes);
     if (e != hipSuccess) {
         b.p = nullptr;
+        (void)hipGetLastError();  // reported here; the next launch's check would report it again
+        h->full = true;
         return fail(h, TPCF_ERR_ALLOC, std::string("hipMalloc: ") + hipGetErrorString(e));
     }
     b.bytes = bytes;
@@ -726,10 +739,35 @@ int64_t subchunk_of(int64_t n, int64_t kc, int64_t share) {
     return k;
 }
 
+// Doubles of one subchunk's partial sums: blocks, then self moments.
+int64_t part_doubles(tpcf_handle h) { return h->gsize + (int64_t)h->nb * (2 * h->lmax + 2); }
+
+// Memory for the partial sums of a chunk's n subchunks, or of as many as there
+// is room for: returns the buffer and how many it holds (0: no room). They go
+// where the chunk's lists are: those have been read when the chunk is
+// contracted, and the next chunk's are written after its sums are reduced.
+// Where that holds too few (a wide operand over few points), d_part takes up
+// to 1/64 of the workspace, and gives it back when that is needed (ensure).
+// (A buffer for all subchunks of a call took 24 GB for 3,000 catalogues of
+// 20,000 points at lmax 10 and 10 bins, as much as half of what else the call
+// needs. A reduction has a row of workgroups per catalogue, so 65535 at most.)
+DevBuf& part_memory(tpcf_handle h, int64_t n, int64_t& room) {
+    const int64_t each = (int64_t)sizeof(double) * part_doubles(h);
+    auto holds = [&](const DevBuf& b) { return (int64_t)b.bytes / each; };
+    n = std::min<int64_t>(n, 65535);
+    if (holds(h->d_list) < n && holds(h->d_part) < n) {
+        int64_t want = std::min(n, std::max<int64_t>(1, h->limit / 64 / each));
+        for (; want > holds(h->d_list); want /= 2)
+            if (ensure(h, h->d_part, (size_t)(want * each)) == TPCF_OK) break;
+    }
+    DevBuf& b = h->d_list.bytes >= h->d_part.bytes ? h->d_list : h->d_part;
+    room = std::min(n, holds(b));
+    return b;
+}
+
 // Splits every catalogue into subchunks and groups whole subchunks into
-// chunks whose a_lm operand and hit lists fit the workspace share. fine:
-// subchunks by the size of the catalogue, else all of kc primaries.
-tpcf_status plan_chunks_of(tpcf_handle h, bool fine) {
+// chunks whose a_lm operand and hit lists fit the workspace share.
+tpcf_status plan_chunks(tpcf_handle h) {
     const int64_t N = h->npts;
     const size_t elem = h->fp64 ? 8 : 4;
     const int64_t per_prim = (int64_t)h->nb * h->NV * (int64_t)elem;
@@ -758,7 +796,7 @@ tpcf_status plan_chunks_of(tpcf_handle h, bool fine) {
     std::vector<double> room(h->ncat);
     for (int c = 0; c < h->ncat; ++c) room[c] = room_of(h->pt_off[c + 1] - h->pt_off[c]);
     h->hits_per_list = hits / h->nb;
-    const double budget = (double)(h->limit / 2);
+    const double budget = h->chunk_budget > 0.0 ? h->chunk_budget : (double)(h->limit / 2);
     // A chunk takes whole subchunks while its primaries stay within 2^23,
     // its operand and predicted list room within the budget, and its list
     // room within 12.8e9 entries (list offsets are 32-bit counts of blocks of
@@ -774,7 +812,7 @@ tpcf_status plan_chunks_of(tpcf_handle h, bool fine) {
     const int64_t share = split ? 16 : 32;
     for (int c = 0; c < h->ncat; ++c) {
         h->cat_sub[c] = (int)h->sub_start.size();
-        const int64_t kc = fine ? subchunk_of(h->pt_off[c + 1] - h->pt_off[c], h->kc, share) : h->kc;
+        const int64_t n = h->pt_off[c + 1] - h->pt_off[c], kc = subchunk_of(n, h->kc, share);
         for (int64_t p = h->pt_off[c]; p < h->pt_off[c + 1]; p += kc) h->sub_start.push_back(p);
     }
     h->cat_sub[h->ncat] = (int)h->sub_start.size();
@@ -783,6 +821,7 @@ tpcf_status plan_chunks_of(tpcf_handle h, bool fine) {
     const int nsub = (int)h->sub_start.size() - 1;
     int s = 0, cat = 0;
     double max_room = 0.0;
+    h->chunk_bytes = 0.0;
     while (s < nsub) {
         Chunk ch;
         ch.sub_begin = s;
@@ -803,6 +842,7 @@ tpcf_status plan_chunks_of(tpcf_handle h, bool fine) {
         ch.sub_end = s;
         ch.p_end = h->sub_start[s];
         max_room = std::max(max_room, r_acc);
+        h->chunk_bytes = std::max(h->chunk_bytes, b_acc);
         h->chunks.push_back(ch);
     }
     int64_t maxch = 0;
@@ -849,17 +889,17 @@ tpcf_status plan_chunks_of(tpcf_handle h, bool fine) {
     if ((st = ensure(h, h->d_subs, sizeof(int) * rel.size() + 64)) != TPCF_OK) return st;
     if ((st = upload(h, h->d_subs, rel.data(), sizeof(int) * rel.size())) != TPCF_OK) return st;
     if ((st = upload(h, h->d_catsub, h->cat_sub.data(), sizeof(int) * (h->ncat + 1))) != TPCF_OK) return st;
-    if ((st = ensure(h, h->d_part, (size_t)nsub * h->gsize * sizeof(double))) != TPCF_OK) return st;
-    const int sw = h->nb * (2 * h->lmax + 2);
-    if ((st = ensure(h, h->d_pself, sizeof(double) * nsub * sw)) != TPCF_OK) return st;
-    return TPCF_OK;
+    if ((st = ensure(h, h->d_G, sizeof(double) * h->ncat * h->gsize)) != TPCF_OK) return st;
+    return ensure(h, h->d_S, sizeof(double) * h->ncat * (part_doubles(h) - h->gsize));
 }
 
-// A workspace with no room for the partial sums of the finer subchunks gets
-// the coarse ones.
-tpcf_status plan_chunks(tpcf_handle h) {
-    const tpcf_status st = plan_chunks_of(h, true);
-    return st == TPCF_ERR_ALLOC ? plan_chunks_of(h, false) : st;
+// Plans chunks of half the largest one's bytes from here on, and gives back what
+// was sized for it. False where every chunk holds one subchunk already.
+bool shrink_chunks(tpcf_handle h) {
+    if (h->chunks.size() + 1 >= h->sub_start.size()) return false;
+    for (DevBuf* b : {&h->d_boff, &h->d_fix, &h->d_cnt, &h->d_A, &h->d_list}) release(h, *b);
+    h->chunk_budget = 0.5 * h->chunk_bytes;
+    return true;
 }
 
 // Pair pass of one chunk: binning, fix-up of the primaries whose predicted
@@ -965,8 +1005,13 @@ tpcf_status pair_chunk(tpcf_handle h, const Chunk& ch) {
     return TPCF_OK;
 }
 
+// Partial sums of a chunk's subchunks and their sums per catalogue, for as many
+// subchunks at a time as there is room.
 tpcf_status contract_chunk(tpcf_handle h, const Chunk& ch) {
-    const int nsub = ch.sub_end - ch.sub_begin;
+    const int sw = h->nb * (2 * h->lmax + 2);
+    int64_t room = 0;
+    double* part = P<double>(part_memory(h, ch.sub_end - ch.sub_begin, room));
+    if (room < 1) return fail(h, TPCF_ERR_ALLOC, "no room for the partial sums of a subchunk: " + h->err);
     Timer t;
     t_begin(h, 3, t);
     ContractArgs c{};
@@ -976,11 +1021,7 @@ tpcf_status contract_chunk(tpcf_handle h, const Chunk& ch) {
     c.p_begin = ch.p_begin;
     c.nb = h->nb;
     c.lmax = h->lmax;
-    c.sub_start = P<int>(h->d_subs) + ch.sub_off;
-    c.nsub = nsub;
-    c.sub_base = ch.sub_begin;
-    c.part32 = nullptr;
-    c.part64 = P<double>(h->d_part);
+    c.part = part;
     c.gsize = h->gsize;
     c.goff = P<int64_t>(h->d_goff);
     // weighted catalogues (data minus randoms) need the six-product split
@@ -989,14 +1030,6 @@ tpcf_status contract_chunk(tpcf_handle h, const Chunk& ch) {
     c.pw = P<float>(h->d_pw);
     c.ks_max = h->contract_step;
     c.lcouple = h->couple >= 0 ? h->couple : h->lmax;
-    if (h->cfg.flags & TPCF_F_ISOTROPIC) {
-        // only the l1 = l2 blocks are formed; the rest of the partials is zero
-        HIPCHK(launch_fill_u64(reinterpret_cast<unsigned long long*>(P<double>(h->d_part) + (int64_t)ch.sub_begin * h->gsize),
-                               (int64_t)nsub * h->gsize, 0ull, h->stream));
-        HIPCHK(launch_contract_iso(c, h->stream));
-    } else {
-        HIPCHK(launch_contract(c, h->stream));
-    }
     SelfArgs s{};
     s.A = h->d_A.p;
     s.ldA = h->ldA;
@@ -1005,35 +1038,36 @@ tpcf_status contract_chunk(tpcf_handle h, const Chunk& ch) {
     s.p_begin = ch.p_begin;
     s.nb = h->nb;
     s.lmax = h->lmax;
-    s.sub_start = P<int>(h->d_subs) + ch.sub_off;
-    s.nsub = nsub;
-    s.sub_base = ch.sub_begin;
-    s.part = P<double>(h->d_pself);
     s.fp64 = h->fp64;
     s.unit_w = h->unit_w ? 1 : 0;
     s.self_lo = h->self_lo ? 1 : 0;
-    HIPCHK(launch_self_moments(s, h->stream));
-    t_end(h, t);
-    return TPCF_OK;
-}
-
-tpcf_status reduce_group(tpcf_handle h) {
-    tpcf_status st;
-    const int sw = h->nb * (2 * h->lmax + 2);
-    if ((st = ensure(h, h->d_G, sizeof(double) * h->ncat * h->gsize)) != TPCF_OK) return st;
-    if ((st = ensure(h, h->d_S, sizeof(double) * h->ncat * sw)) != TPCF_OK) return st;
-    Timer t;
-    t_begin(h, 3, t);
-    ReduceArgs a{};
-    a.part[0] = P<double>(h->d_part);
-    a.part[1] = P<double>(h->d_pself);
-    a.out[0] = P<double>(h->d_G);
-    a.out[1] = P<double>(h->d_S);
-    a.width[0] = h->gsize;
-    a.width[1] = sw;
-    a.cat_sub = P<int>(h->d_catsub);
-    a.ncat = h->ncat;
-    HIPCHK(launch_reduce_partials(a, h->stream));
+    ReduceArgs r{};
+    r.part[0] = part;
+    r.out[0] = P<double>(h->d_G);
+    r.out[1] = P<double>(h->d_S);
+    r.width[0] = h->gsize;
+    r.width[1] = sw;
+    r.cat_sub = P<int>(h->d_catsub);
+    for (int lo = ch.sub_begin; lo < ch.sub_end; lo += (int)room) {
+        const int hi = std::min(ch.sub_end, lo + (int)room);
+        c.sub_start = s.sub_start = P<int>(h->d_subs) + ch.sub_off + (lo - ch.sub_begin);
+        c.nsub = s.nsub = hi - lo;
+        s.part = part + c.nsub * h->gsize;
+        if (h->cfg.flags & TPCF_F_ISOTROPIC) {
+            // only the l1 = l2 blocks are formed; the rest of the partials is zero
+            HIPCHK(launch_fill_u64(reinterpret_cast<unsigned long long*>(part), c.nsub * h->gsize, 0ull, h->stream));
+            HIPCHK(launch_contract_iso(c, h->stream));
+        } else {
+            HIPCHK(launch_contract(c, h->stream));
+        }
+        HIPCHK(launch_self_moments(s, h->stream));
+        r.part[1] = s.part;
+        r.sub_lo = lo;
+        r.sub_hi = hi;
+        r.cat_lo = (int)(std::upper_bound(h->cat_sub.begin(), h->cat_sub.end(), lo) - h->cat_sub.begin()) - 1;
+        r.ncat = (int)(std::lower_bound(h->cat_sub.begin(), h->cat_sub.end(), hi) - h->cat_sub.begin()) - r.cat_lo;
+        HIPCHK(launch_reduce_partials(r, h->stream));
+    }
     t_end(h, t);
     return TPCF_OK;
 }
@@ -1135,6 +1169,24 @@ tpcf_status pair_pass(tpcf_handle h, bool contract_now) {
         h->list_cap = ncap;
         h->list_grow = std::min(h->list_grow * 2.0, 64.0);  // kept for the next groups and calls
         if ((st = ensure(h, h->d_list, (size_t)list_elem_bytes(h) * h->list_cap)) != TPCF_OK) return st;
+    }
+}
+
+// Plan and pair pass, contracted chunk by chunk where there are several (or with
+// contract_now). What does not fit the workspace is tried in smaller chunks,
+// which the handle keeps for its later passes, as it keeps the lists' growth:
+// results do not depend on the chunks.
+tpcf_status run_pass(tpcf_handle h, bool contract_now) {
+    const double budget = h->chunk_budget;
+    for (;;) {
+        h->full = false;
+        tpcf_status st = plan_chunks(h);
+        if (st == TPCF_OK) st = pair_pass(h, contract_now || h->chunks.size() > 1);
+        if (st == TPCF_OK) return st;
+        if (st != TPCF_ERR_ALLOC || !h->full || !shrink_chunks(h)) {
+            h->chunk_budget = budget;
+            return st;
+        }
     }
 }
 
@@ -1263,7 +1315,6 @@ tpcf_status run_groups(tpcf_handle h, int32_t ncat, const int64_t* h_n, const in
             c0 = c1;
             continue;
         }
-        if ((st = plan_chunks(h)) != TPCF_OK) return st;
         // The self moments of order above lmax cancel from every multipole
         // of L <= lmax (their coefficients sum to zero over m), and this run
         // keeps no per-m sums: the harmonic pass may stop them at lmax.
@@ -1275,11 +1326,10 @@ tpcf_status run_groups(tpcf_handle h, int32_t ncat, const int64_t* h_n, const in
         for (int t = 0; t < n_mult; ++t) lc = std::max(lc, std::abs(h_l1l2L[3 * t] - h_l1l2L[3 * t + 1]));
         h->couple = n_mult > 0 && lc < h->lmax ? lc : -1;
         h->couple_cut = h->couple;
-        st = pair_pass(h, true);
+        st = run_pass(h, true);
         h->self_lo = false;
         h->couple = -1;
         if (st != TPCF_OK) return st;
-        if ((st = reduce_group(h)) != TPCF_OK) return st;
         h->stage = 3;
         if (d_out && (st = finalize_group(h, n_mult, h_l1l2L, d_out + per_out * c0)) != TPCF_OK) return st;
         pos_off += pts;
@@ -1352,7 +1402,7 @@ void tpcf_destroy(tpcf_handle h) {
                      &h->d_vol, &h->d_scale, &h->d_sign_scale, &h->d_gaunt, &h->d_pt_off, &h->d_cellid,
                      &h->d_count, &h->d_start, &h->d_slab, &h->d_cursor, &h->d_tmp, &h->d_tmpz, &h->d_orig, &h->d_pf, &h->d_pw,
                      &h->d_pa, &h->d_istart, &h->d_icell, &h->d_scanw, &h->d_catbad, &h->d_pd, &h->d_perm, &h->d_catid, &h->d_flag, &h->d_list, &h->d_fix, &h->d_lcursor, &h->d_boff,
-                     &h->d_cnt, &h->d_A, &h->d_subs, &h->d_catsub, &h->d_part, &h->d_pself, &h->d_G,
+                     &h->d_cnt, &h->d_A, &h->d_subs, &h->d_catsub, &h->d_part, &h->d_G,
                      &h->d_S, &h->d_nd, &h->d_mult, &h->d_coefG, &h->d_coefS, &h->d_lflag,
                      &h->d_xiq, &h->d_xicoef, &h->d_xirr, &h->d_xiruns, &h->d_covx, &h->d_covoff,
                      &h->d_covflag, &h->d_covpart, &h->d_edgeT, &h->d_egaunt, &h->d_eunits, &h->d_errr,
@@ -1390,13 +1440,12 @@ tpcf_status tpcf_alm_accumulate(tpcf_handle h) {
     HIPCHK(hipSetDevice(h->device));
     tpcf_status st = check_nonfinite(h);
     if (st != TPCF_OK) return st;
-    if ((st = plan_chunks(h)) != TPCF_OK) return st;
-    const bool single = h->chunks.size() == 1;
     // the step calls keep every self-moment order and every block (h->self_lo
     // is false and h->couple is -1 here)
     h->self_cut = h->self_lo;
     h->couple_cut = h->couple;
-    if ((st = pair_pass(h, !single)) != TPCF_OK) return st;
+    if ((st = run_pass(h, false)) != TPCF_OK) return st;
+    const bool single = h->chunks.size() == 1;
     h->alm_kept = single;
     h->contracted_in_pass = !single;
     h->pairs_valid = false;
@@ -1436,7 +1485,6 @@ tpcf_status tpcf_contract(tpcf_handle h, double* d_nnn_out) {
         if (!h->contracted_in_pass)
             for (const Chunk& ch : h->chunks)
                 if ((st = contract_chunk(h, ch)) != TPCF_OK) return st;
-        if ((st = reduce_group(h)) != TPCF_OK) return st;
         h->stage = 3;
     }
     if (d_nnn_out) {
@@ -1789,10 +1837,10 @@ tpcf_status tpcf_autotune(tpcf_handle h, const double* d_pos, const double* d_w,
         if (h->g.k == last_k || (h->g.k != k && !h->g.single)) continue;  // not admissible: fell back
         last_k = h->g.k;
         if ((st = check_nonfinite(h)) != TPCF_OK) break;
-        if (nmu == 0 && (st = plan_chunks(h)) != TPCF_OK) break;
-        // one untimed pass, then the timed one
+        // an untimed pass (which also settles the chunks), then the timed one
+        if (nmu == 0 && (st = run_pass(h, false)) != TPCF_OK) break;
         double ms = 0.0;
-        for (int rep = 0; rep < 2 && st == TPCF_OK; ++rep) {
+        for (int rep = nmu > 0 ? 0 : 1; rep < 2 && st == TPCF_OK; ++rep) {
             if (hipEventRecord(e0, h->stream) != hipSuccess) { st = fail(h, TPCF_ERR_DEVICE, "hipEventRecord"); break; }
             st = nmu > 0 ? tpcf_xi_count(h, nmu, d_counts) : pair_pass(h, false);
             if (st != TPCF_OK) break;

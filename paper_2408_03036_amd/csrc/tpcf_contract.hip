@@ -246,7 +246,7 @@ __global__ void __launch_bounds__(64 * kF64Waves) k_contract_f64(ContractArgs a,
         if (st + 1 < nsteps) store(st + 1, nbuf == 2 ? (st + 1) & 1 : 0, R);
         __syncthreads();
     }
-    double* G = a.part64 + (int64_t)(a.sub_base + s) * a.gsize + a.goff[m];
+    double* G = a.part + (int64_t)s * a.gsize + a.goff[m];
 #pragma unroll
     for (int q = 0; q < TPW; ++q) {
         if (q >= nq) continue;
@@ -389,7 +389,7 @@ __global__ void __launch_bounds__(64 * kF32Waves) k_contract_f32(ContractArgs a,
         if (st + 1 < nsteps) store(st + 1, (st + 1) & 1, R);
         __syncthreads();
     }
-    double* G = a.part64 + (int64_t)(a.sub_base + s) * a.gsize + a.goff[m];
+    double* G = a.part + (int64_t)s * a.gsize + a.goff[m];
 #pragma unroll
     for (int q = 0; q < TPW; ++q) {
         if (q >= nq) continue;
@@ -561,7 +561,7 @@ __global__ void __launch_bounds__(64 * kIsoWaves) k_contract_iso(ContractArgs a)
         if (it + 1 < nit) step(it + 1, sB);
     }
     // upper triangle of the block: tiles (0,0), (0,1), (1,1)
-    const int64_t base = (int64_t)(a.sub_base + s) * a.gsize + a.goff[m];
+    const int64_t base = (int64_t)s * a.gsize + a.goff[m];
     const int j = lane & 15;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -572,7 +572,7 @@ __global__ void __launch_bounds__(64 * kIsoWaves) k_contract_iso(ContractArgs a)
             // output rows of a 16x16 MFMA: FP64 lane / 16 + 4 r, FP32 4 (lane / 16) + r
             const int c1r = 16 * ti + (F32 ? 4 * (lane >> 4) + r : (lane >> 4) + 4 * r), c2 = 16 * tj + j;
             if (c1r < nb && c2 < nb && c1r <= c2)
-                a.part64[base + (int64_t)(c1r * nl + (l - m)) * K + c2 * nl + (l - m)] =
+                a.part[base + (int64_t)(c1r * nl + (l - m)) * K + c2 * nl + (l - m)] =
                     F32 ? accd[q][r] : acc[q][r];
         }
     }
@@ -845,7 +845,7 @@ __global__ void __launch_bounds__(64 * kBfWaves) k_contract_bf16(ContractArgs a,
             __syncthreads();
         }
     }
-    double* G = a.part64 + (int64_t)(a.sub_base + s) * a.gsize + a.goff[m];
+    double* G = a.part + (int64_t)s * a.gsize + a.goff[m];
 #pragma unroll
     for (int q = 0; q < kBfTPW; ++q) {
         if (q >= nq) continue;
@@ -929,7 +929,7 @@ __global__ void __launch_bounds__(256) k_self_moments(SelfArgs a) {
         double sum = (acc[0] + acc[1]) + (acc[2] + acc[3]);
         for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
         if (lane == 0) {
-            double* out = a.part + (int64_t)(a.sub_base + s) * a.nb * width;
+            double* out = a.part + (int64_t)s * a.nb * width;
             out[task] = sum;
             if (UNIT && L == 0) out[b * width + nL] = sum;
         }
@@ -938,17 +938,21 @@ __global__ void __launch_bounds__(256) k_self_moments(SelfArgs a) {
 
 // Sums of each catalogue's subchunks, those of the contraction and of the self
 // moments in one launch. Latency bound: a thread adds one value of a few dozen
-// subchunks in their order, eight loads in flight.
+// subchunks in their order, eight loads in flight. A catalogue whose subchunks
+// come in several launches goes on from the sum so far, so that its sum does
+// not depend on how they are cut.
 __global__ void k_reduce_partials(ReduceArgs a) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int c = blockIdx.y;
+    const int c = a.cat_lo + blockIdx.y;
     if (i >= a.width[0] + a.width[1]) return;
     const int k = i >= a.width[0];
     const int64_t width = a.width[k], e = k ? i - a.width[0] : i;
     const double* p = a.part[k] + e;
-    const int q1 = a.cat_sub[c + 1];
-    double s = 0.0;
-    int q = a.cat_sub[c];
+    double* out = a.out[k] + c * width + e;
+    const int first = a.cat_sub[c];
+    const int q1 = min(a.cat_sub[c + 1], a.sub_hi) - a.sub_lo;
+    int q = max(first, a.sub_lo) - a.sub_lo;
+    double s = first >= a.sub_lo ? 0.0 : *out;
     for (; q + 8 <= q1; q += 8) {
         double v[8];
 #pragma unroll
@@ -957,7 +961,7 @@ __global__ void k_reduce_partials(ReduceArgs a) {
         for (int u = 0; u < 8; ++u) s += v[u];
     }
     for (; q < q1; ++q) s += p[q * width];
-    a.out[k][c * width + e] = s;
+    *out = s;
 }
 
 __global__ void k_finalize(FinalArgs a) {

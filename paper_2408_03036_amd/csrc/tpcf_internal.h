@@ -239,9 +239,7 @@ struct ContractArgs {
     int nb, lmax;
     const int* sub_start;    // [nsub+1] chunk-relative first primary of each subchunk
     int nsub;
-    int sub_base;            // global index of the first subchunk of this chunk
-    float* part32;           // partial sums (FP32 modes): [nsub_total][gsize]
-    double* part64;          // partial sums (FP64 mode)
+    double* part;            // partial sums: [nsub][gsize]
     int64_t gsize;           // sum_m K_m^2
     const int64_t* goff;     // [lmax+1] offset of G_m inside a partial
     int mode;                // 0 fp64, 1 fp32, 2 bf16x3, 3 bf16x6
@@ -264,21 +262,22 @@ struct SelfArgs {
     int nb, lmax;
     const int* sub_start;
     int nsub;
-    int sub_base;
-    double* part;            // [nsub_total][nb*(2lmax+2)]: moments then pair count per bin
+    double* part;            // [nsub][nb*(2lmax+2)]: moments then pair count per bin
     int fp64;
     int unit_w;              // all weights 1 (pd[].w not read)
     int self_lo;             // orders above lmax neither written by the harmonic pass nor read: zero
 };
 hipError_t launch_self_moments(const SelfArgs& a, hipStream_t s);
 
-// Fixed-order sums of subchunk partials per catalogue.
+// Adds the partials of subchunks sub_lo .. sub_hi - 1, in their order, to the
+// sums of the ncat catalogues from cat_lo on that hold them; a catalogue's sum
+// starts with its first subchunk.
 struct ReduceArgs {
-    const double* part[2];  // [subchunk][width]: contraction, self moments
+    const double* part[2];  // [sub_hi - sub_lo][width]: contraction, self moments
     double* out[2];         // [catalogue][width]
     int64_t width[2];
-    const int* cat_sub;     // [ncat+1]
-    int ncat;
+    const int* cat_sub;     // first subchunk of every catalogue, and the end
+    int sub_lo, sub_hi, cat_lo, ncat;
 };
 hipError_t launch_reduce_partials(const ReduceArgs& a, hipStream_t s);
 

@@ -1,0 +1,67 @@
+"""Workspace limits: what a call needs does not grow with the way its sums are
+split, and results do not depend on the limit, the chunks or the grouping."""
+import numpy as np
+import pytest
+
+from paper_2408_03036_amd import catalogs as C
+from paper_2408_03036_amd import tpcf as T
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as _t
+    assert _t.cuda.is_available(), "GPU tests need a GPU"
+    T.load()
+    return _t
+
+
+# (catalogues, points, lmax, bins, precision, limits in MiB). The arrays of a
+# call with 4,096 primaries to a partial sum fit every one of these limits; a
+# buffer for the partial sums of all finer subchunks (130 MB for the first)
+# does not, or not beside the catalogues' sums.
+@pytest.mark.parametrize("ncat,n,lmax,nb,prec,limits", [
+    (40, 2000, 10, 10, T.PREC_MIXED_BF16X3, (82, 100, 110, 150, 320)),
+    (40, 2000, 4, 12, T.PREC_FP32, (42, 50, 60, 80)),
+    (12, 3000, 10, 10, T.PREC_FP64, (54, 80, 120, 135))])
+def test_small_workspaces(torch, ncat, n, lmax, nb, prec, limits):
+    """A batch runs in each of these workspaces, and every catalogue's
+    multipoles are, bit for bit, those of the step calls with room for all."""
+    box, edges = 1000.0, np.linspace(24.0, 120.0, nb + 1)
+    mults = [(l, l, 0) for l in range(lmax + 1)]
+    pos = torch.from_numpy(np.vstack([C.poisson(n, box, 50 + c) for c in range(ncat)])).cuda()
+    h = T.Handle(box, edges, lmax, precision=prec)
+    alone = []
+    for c in (0, ncat // 2, ncat - 1):
+        h.build_grid(pos[c * n:(c + 1) * n].contiguous())
+        h.alm_accumulate()
+        h.contract()
+        alone.append(h.multipoles(mults).cpu().numpy())
+    h.close()
+    for limit in limits:
+        print(f"  limit {limit} MiB", flush=True)
+        h = T.Handle(box, edges, lmax, precision=prec, workspace_limit=limit << 20)
+        for _ in range(2):  # the second call finds the buffers of the first
+            got = h.run_catalogs([n] * ncat, [n] * ncat, pos, None, mults).cpu().numpy()
+            for c, ref in zip((0, ncat // 2, ncat - 1), alone):
+                assert np.array_equal(got[c], ref)
+        h.close()
+
+
+# Partial sums held a few subchunks at a time: 14.6 MB each at 32 bins and lmax
+# 16 (one at a time in the smaller workspace, all in the default one), and
+# catalogues that begin and end inside such a span
+@pytest.mark.parametrize("prec,isotropic,limit", [(T.PREC_FP32, False, 420), (T.PREC_FP64, True, 700)])
+def test_partial_sums_in_spans(torch, prec, isotropic, limit):
+    box, edges, lmax = 1000.0, np.linspace(20.0, 120.0, 33), 16
+    sizes = [1500, 3, 700, 900]
+    mults = [(l, l, 0) for l in range(lmax + 1)]
+    flags = T.F_ISOTROPIC if isotropic else 0
+    pos = torch.from_numpy(np.vstack([C.poisson(k, box, 90 + i) for i, k in enumerate(sizes)])).cuda()
+    out = []
+    for lim in (0, limit << 20):
+        h = T.Handle(box, edges, lmax, precision=prec, flags=flags, workspace_limit=lim)
+        out.append(h.run_catalogs(sizes, sizes, pos, None, mults).cpu().numpy())
+        h.close()
+    assert np.array_equal(out[0], out[1])
