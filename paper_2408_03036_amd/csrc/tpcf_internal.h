@@ -278,6 +278,8 @@ struct ReduceArgs {
     int64_t width[2];
     const int* cat_sub;     // first subchunk of every catalogue, and the end
     int sub_lo, sub_hi, cat_lo, ncat;
+    const int64_t* goff;    // [lmax+2] offset of G_m inside a sum, and the end
+    int nb, lmax, lcouple;  // blocks with |l1 - l2| > lcouple are not formed
 };
 hipError_t launch_reduce_partials(const ReduceArgs& a, hipStream_t s);
 

@@ -2,6 +2,7 @@
 split, and results do not depend on the limit, the chunks or the grouping."""
 import numpy as np
 import pytest
+import test_gpu_shape_edges as edges_of
 
 from paper_2408_03036_amd import catalogs as C
 from paper_2408_03036_amd import tpcf as T
@@ -65,3 +66,12 @@ def test_partial_sums_in_spans(torch, prec, isotropic, limit):
         out.append(h.run_catalogs(sizes, sizes, pos, None, mults).cpu().numpy())
         h.close()
     assert np.array_equal(out[0], out[1])
+
+
+# Wide operands, whose subchunks hold 512 primaries at least: 16 bins at lmax 15
+# one primary below and above the first boundary and past the second, and the
+# widest operand
+@pytest.mark.parametrize("n,nb,lmax", [(511, 16, 15), (513, 16, 15), (1030, 16, 15), (520, 32, 16)])
+@pytest.mark.parametrize("prec,weighted", [(T.PREC_FP64, False), (T.PREC_FP32, True), (T.PREC_MIXED_BF16X6, False)])
+def test_contraction_of_wide_operands(torch, n, nb, lmax, prec, weighted):
+    edges_of.test_contraction_of_exported_alm(torch, n, nb, lmax, prec, weighted)
