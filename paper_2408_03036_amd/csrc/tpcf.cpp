@@ -89,7 +89,7 @@ struct tpcf_handle_s {
     bool self_cut = false;  // the summed self moments stop at order lmax (set by such a run)
     int couple = -1;        // this pass's contraction may skip blocks with |l1 - l2| > couple (-1: none)
     int couple_cut = -1;    // the summed blocks stop at |l1 - l2| <= couple_cut (set by tpcf_run_catalogs)
-    DevBuf d_pt_off, d_cellid, d_count, d_start, d_slab, d_cursor, d_tmp, d_tmpz, d_orig, d_pf, d_pw, d_pa, d_pd, d_perm,
+    DevBuf d_pt_off, d_cellid, d_count, d_start, d_cursor, d_tmp, d_tmpz, d_orig, d_pf, d_pw, d_pa, d_pd, d_perm,
         d_catid, d_flag, d_istart, d_icell, d_scanw, d_catbad;
     std::vector<int32_t> cat_status;  // per catalogue of the last tpcf_run_catalogs
     std::vector<int> item_cat;       // [ncat+1] first work item of each catalogue
@@ -656,13 +656,8 @@ tpcf_status build_grid_group(tpcf_handle h, const double* d_pos, const double* d
     const int64_t MS = M * h->g.zsub;
     if ((st = upload(h, h->d_pt_off, h->pt_off.data(), sizeof(int64_t) * (h->ncat + 1))) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_cellid, sizeof(int) * N)) != TPCF_OK) return st;
-    if ((st = ensure(h, h->d_count, sizeof(int) * (MS + 1))) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_start, sizeof(int) * (M + 1))) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_istart, sizeof(int) * (M + 1))) != TPCF_OK) return st;
-    if (MS > M && (st = ensure(h, h->d_slab, sizeof(int) * (MS + 1))) != TPCF_OK) return st;
-    if ((st = ensure(h, h->d_scanw, sizeof(int) * grid_scan_work_ints(MS))) != TPCF_OK) return st;
-    if ((st = ensure(h, h->d_cursor, sizeof(int) * (MS + 1))) != TPCF_OK) return st;
-    int* slab = MS > M ? P<int>(h->d_slab) : P<int>(h->d_start);
     if ((st = ensure(h, h->d_tmp, sizeof(int) * N)) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_tmpz, sizeof(double) * N)) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_orig, sizeof(int) * N)) != TPCF_OK) return st;
@@ -671,32 +666,49 @@ tpcf_status build_grid_group(tpcf_handle h, const double* d_pos, const double* d
     if ((st = ensure(h, h->d_pw, sizeof(float) * (N + 16))) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_pa, sizeof(float4) * N)) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_pd, sizeof(double4) * N)) != TPCF_OK) return st;
+    // Counters of the sort. Those of slabs, at most N / 16 each, lie in the
+    // memory of the sorted points, which are written after their last use.
+    int *count = nullptr, *cursor = nullptr, *slab = nullptr, *scanw = nullptr;
+    if (MS > M) {
+        const int64_t step = (MS + 1 + 63) / 64 * 64;
+        if ((int64_t)sizeof(int) * (3 * step + grid_scan_work_ints(MS)) > (int64_t)h->d_pd.bytes)
+            return fail(h, TPCF_ERR_DEVICE, "slab counters larger than the points");
+        count = P<int>(h->d_pd);
+        cursor = count + step;
+        slab = cursor + step;
+        scanw = slab + step;
+    } else {
+        if ((st = ensure(h, h->d_count, sizeof(int) * (M + 1))) != TPCF_OK) return st;
+        if ((st = ensure(h, h->d_cursor, sizeof(int) * (M + 1))) != TPCF_OK) return st;
+        if ((st = ensure(h, h->d_scanw, sizeof(int) * grid_scan_work_ints(M))) != TPCF_OK) return st;
+        count = P<int>(h->d_count);
+        cursor = P<int>(h->d_cursor);
+        slab = P<int>(h->d_start);
+        scanw = P<int>(h->d_scanw);
+    }
     if ((st = ensure(h, h->d_perm, sizeof(int) * N)) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_catid, sizeof(int) * N)) != TPCF_OK) return st;
+    // work items of the binning pass: blocks of up to kItemPrims primaries of one cell
+    if ((st = ensure(h, h->d_icell, sizeof(int) * (M + N / kItemPrims + 1))) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_flag, sizeof(int) * 4)) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_catbad, sizeof(int) * h->ncat)) != TPCF_OK) return st;
     if ((st = ensure_host(h, (size_t)h->ncat + 6)) != TPCF_OK) return st;
     Timer t;
     t_begin(h, 0, t);
-    if ((st = clear(h, {{h->d_count.p, MS + 1}, {h->d_cursor.p, MS + 1}, {h->d_flag.p, 4}, {h->d_catbad.p, h->ncat}})) !=
-        TPCF_OK)
+    if ((st = clear(h, {{count, MS + 1}, {cursor, MS + 1}, {h->d_flag.p, 4}, {h->d_catbad.p, h->ncat}})) != TPCF_OK)
         return st;
     HIPCHK(launch_grid_assign(d_pos, d_w, N, P<int64_t>(h->d_pt_off), h->ncat, h->g, P<int>(h->d_cellid),
-                              P<int>(h->d_count), P<int>(h->d_flag), P<int>(h->d_catbad), h->stream));
+                              count, P<int>(h->d_flag), P<int>(h->d_catbad), h->stream));
     // a cell's count gives its work items too, a slab's does not
-    HIPCHK(launch_grid_scan(P<int>(h->d_count), MS, slab, MS > M ? nullptr : P<int>(h->d_istart), P<int>(h->d_scanw),
-                            h->stream));
+    HIPCHK(launch_grid_scan(count, MS, slab, MS > M ? nullptr : P<int>(h->d_istart), scanw, h->stream));
     if (MS > M) HIPCHK(launch_grid_cells(slab, M, h->g.zsub, P<int>(h->d_start), h->stream));
-    HIPCHK(launch_grid_scatter(P<int>(h->d_cellid), N, h->g, slab, P<int>(h->d_cursor), d_pos, P<int>(h->d_tmp),
+    HIPCHK(launch_grid_scatter(P<int>(h->d_cellid), N, h->g, slab, cursor, d_pos, P<int>(h->d_tmp),
                                P<double>(h->d_tmpz), h->stream));
     HIPCHK(launch_grid_order(P<int>(h->d_cellid), N, h->g, slab, P<int>(h->d_tmp), P<double>(h->d_tmpz),
                              P<int>(h->d_orig), h->stream));
-    // work items of the binning pass: blocks of up to kItemPrims primaries of one cell
-    const int64_t nitems_max = M + N / kItemPrims + 1;
-    if ((st = ensure(h, h->d_icell, sizeof(int) * nitems_max)) != TPCF_OK) return st;
     if (MS > M) {
-        HIPCHK(launch_items_count(P<int>(h->d_start), M, P<int>(h->d_cursor), h->stream));
-        HIPCHK(launch_grid_scan(P<int>(h->d_cursor), M, P<int>(h->d_istart), nullptr, P<int>(h->d_scanw), h->stream));
+        HIPCHK(launch_items_count(P<int>(h->d_start), M, cursor, h->stream));
+        HIPCHK(launch_grid_scan(cursor, M, P<int>(h->d_istart), nullptr, scanw, h->stream));
     }
     HIPCHK(launch_grid_fill(d_pos, d_w, N, P<int>(h->d_orig), P<int>(h->d_cellid), h->g, P<float4>(h->d_pf),
                             P<float>(h->d_pw), P<float4>(h->d_pa), P<double4>(h->d_pd), P<int>(h->d_perm), P<int>(h->d_catid),
@@ -1411,7 +1423,7 @@ void tpcf_destroy(tpcf_handle h) {
     }
     DevBuf* all[] = {&h->d_e2, &h->d_e2f, &h->d_guard, &h->d_runs, &h->d_shift_f, &h->d_goff,
                      &h->d_vol, &h->d_scale, &h->d_sign_scale, &h->d_gaunt, &h->d_pt_off, &h->d_cellid,
-                     &h->d_count, &h->d_start, &h->d_slab, &h->d_cursor, &h->d_tmp, &h->d_tmpz, &h->d_orig, &h->d_pf, &h->d_pw,
+                     &h->d_count, &h->d_start, &h->d_cursor, &h->d_tmp, &h->d_tmpz, &h->d_orig, &h->d_pf, &h->d_pw,
                      &h->d_pa, &h->d_istart, &h->d_icell, &h->d_scanw, &h->d_catbad, &h->d_pd, &h->d_perm, &h->d_catid, &h->d_flag, &h->d_list, &h->d_fix, &h->d_lcursor, &h->d_boff,
                      &h->d_cnt, &h->d_A, &h->d_subs, &h->d_catsub, &h->d_part, &h->d_G,
                      &h->d_S, &h->d_nd, &h->d_mult, &h->d_coefG, &h->d_coefS, &h->d_lflag,

@@ -75,3 +75,14 @@ def test_partial_sums_in_spans(torch, prec, isotropic, limit):
 @pytest.mark.parametrize("prec,weighted", [(T.PREC_FP64, False), (T.PREC_FP32, True), (T.PREC_MIXED_BF16X6, False)])
 def test_contraction_of_wide_operands(torch, n, nb, lmax, prec, weighted):
     edges_of.test_contraction_of_exported_alm(torch, n, nb, lmax, prec, weighted)
+
+
+def test_crowded_cells_need_no_room(torch):
+    """The arrays of a grid take 96 bytes per point and 4 per work item of 16
+    points; the counters of a crowded cell's slabs (0.75 bytes per point) fit
+    beside them in no more room than that."""
+    n = 1_000_000
+    pos = torch.from_numpy(C.poisson(n, 100.0, 8)).cuda()
+    h = T.Handle(100.0, np.linspace(10.0, 50.0, 3), 0, workspace_limit=int(96.5 * n))
+    h.build_grid(pos)
+    h.close()
