@@ -263,11 +263,15 @@ tpcf_status ensure_host(tpcf_handle h, size_t n) {
     void* p = nullptr;
     const hipError_t e = hipHostMalloc(&p, n * sizeof(int), hipHostMallocMapped);
     if (e != hipSuccess) return fail(h, TPCF_ERR_ALLOC, std::string("hipHostMalloc: ") + hipGetErrorString(e));
-    h->host = static_cast<int*>(p);
-    h->host_ints = n;
     void* d = nullptr;
-    HIPCHK(hipHostGetDevicePointer(&d, p, 0));
+    const hipError_t ed = hipHostGetDevicePointer(&d, p, 0);
+    if (ed != hipSuccess || !d) {
+        hipHostFree(p);
+        return fail(h, TPCF_ERR_DEVICE, std::string("hipHostGetDevicePointer: ") + hipGetErrorString(ed));
+    }
+    h->host = static_cast<int*>(p);
     h->host_dev = static_cast<int*>(d);
+    h->host_ints = n;
     return TPCF_OK;
 }
 
@@ -1399,7 +1403,9 @@ tpcf_status tpcf_create(const tpcf_config* cfg, int device, void* hip_stream, tp
         tpcf_destroy(h);
         return TPCF_ERR_DEVICE;
     }
-    st = setup_constants(h);
+    // the pinned memory, here and not in the first call that reads a flag
+    st = ensure_host(h, 1);
+    if (st == TPCF_OK) st = setup_constants(h);
     if (st != TPCF_OK) {
         tpcf_destroy(h);
         return st;
