@@ -359,9 +359,10 @@ __global__ void __launch_bounds__(64 * kXW) k_xi_count(XiArgs a) {
                     bool near;
                     if constexpr (UNIFORM) {
                         // the shells in bin units, widened by a guard band that
-                        // lies inside the one of the near test
+                        // lies inside the one of the near test (a separation
+                        // whose square overflows has u = NaN, and is outside)
                         const float uu = fmaf(r2v[g] * rinv, a.inv_dr, ne0);
-                        if (fabsf(uu - half_nb) > a.reach_u) continue;
+                        if (!(fabsf(uu - half_nb) <= a.reach_u)) continue;
                         near = fabsf(__builtin_amdgcn_fractf(uu) - 0.5f) > 0.5f - a.delta;
                         bb = (int)uu;
                     } else {
