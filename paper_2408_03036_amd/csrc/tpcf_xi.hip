@@ -352,9 +352,9 @@ __global__ void __launch_bounds__(64 * kXW) k_xi_count(XiArgs a) {
 #pragma unroll
                 for (int g = 0; g < kXG; ++g) {
                     if (g >= ng) break;
-                    // 1 / r, also for r = 0 and denormal r^2: r is then 0, and
-                    // the guard band of t sends the pair to the exact path
-                    const float rinv = __builtin_amdgcn_rsqf(fmaxf(r2v[g], 1e-30f));
+                    // 1 / r, of at least the smallest normal r^2: with r = 0 the
+                    // guard bands send the pair to the exact path
+                    const float rinv = __builtin_amdgcn_rsqf(fmaxf(r2v[g], 1.17549435e-38f));
                     int bb;
                     bool near;
                     if constexpr (UNIFORM) {

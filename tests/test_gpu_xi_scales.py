@@ -41,3 +41,10 @@ def counts_at(torch, scale, lo, hi, spacing, nmu):
 def test_squares_past_the_largest_float(torch, lo, hi, spacing, nmu):
     got, ref = counts_at(torch, 2.0**65, lo, hi, spacing, nmu)
     assert np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("spacing", ["linear", "log"])
+@pytest.mark.parametrize("lo,hi", [(0.05, 0.45), (0.05, 0.3)])
+def test_separations_below_1e15(torch, lo, hi, spacing):
+    got, ref = counts_at(torch, 2.0**-50, lo, hi, spacing, 7)
+    assert np.array_equal(got, ref)
