@@ -1008,6 +1008,8 @@ tpcf_status pair_chunk(tpcf_handle h, const Chunk& ch) {
     a.p_end = ch.p_end;
     a.list = h->fp64 ? P<uint32_t>(h->d_list) : nullptr;
     a.rec = h->fp64 ? nullptr : P<float4>(h->d_list);
+    a.inv_box = 1.0 / h->g.box;
+    if (std::fma(a.inv_box, h->g.box, -1.0) < 0.0) a.inv_box = std::nextafter(a.inv_box, HUGE_VAL);
     a.unit_w = h->unit_w ? 1 : 0;
     // a wavefront per list once lists average 256 records or more (the
     // predicted hits of a primary of the densest catalogue, over the bins)

@@ -145,6 +145,7 @@ struct AlmArgs {
     const int* catid;
     const int64_t* pt_off;
     Grid g;
+    double inv_box;          // 1 / box, rounded up
     int nb;
     int lmax;
     int64_t p_begin, p_end;

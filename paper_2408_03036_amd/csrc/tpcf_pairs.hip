@@ -897,7 +897,9 @@ __device__ __forceinline__ double weight_of(const double4& d) { return d.w; }
 
 // Direction of the minimum-image separation of two points of the box (FP64).
 // Positions lie in [0, L) and a listed pair is never half a box apart, so
-// the count of periods is -1, 0 or 1 and the product with it is exact.
+// the count of periods is -1, 0 or 1 and the product with it is exact. inv_L is
+// 1 / L rounded up: half a box and one ulp then gives more than 1/2 after the
+// rounding of the product, half a box less one ulp does not.
 template <class Pt>
 __device__ __forceinline__ Dir<double> unit_direction(const Pt& d, const double4& P, double L, double inv_L) {
     double dx = d.x - P.x, dy = d.y - P.y, dz = d.z - P.z;
@@ -1106,7 +1108,7 @@ __device__ __forceinline__ void alm_part(const AlmArgs& a, T* smem) {
         for (int i = 0; i < KG; ++i) {
             Dir<T> u;
             if constexpr (F64) {
-                u = unit_direction(src[i], P64, a.g.box, 1.0 / a.g.box);
+                u = unit_direction(src[i], P64, a.g.box, a.inv_box);
             } else {
                 const float inv = __builtin_amdgcn_rsqf(src[i].x * src[i].x + src[i].y * src[i].y + src[i].z * src[i].z);
                 u = {src[i].x * inv, src[i].y * inv, src[i].z * inv, src[i].w};
