@@ -181,8 +181,11 @@ constexpr int kIB = 32;
 constexpr int kIS = kIB + 1;
 
 // 1 / x to within an ulp or so: the hardware's estimate and two Newton steps
-// (a division is on the critical path of every pivot).
+// (a division is on the critical path of every pivot). Where the estimate or a
+// step would leave the normal numbers, and for an infinite variance (the
+// precision is then 0), it is the division.
 __device__ __forceinline__ double fast_inverse(double x) {
+    if (!(x > 0x1p-1000 && x < 0x1p1000)) return 1.0 / x;
     double y = __builtin_amdgcn_rcp(x);
     y = fma(y, fma(-x, y, 1.0), y);
     return fma(y, fma(-x, y, 1.0), y);
