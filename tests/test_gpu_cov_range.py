@@ -57,3 +57,18 @@ def test_variances_near_the_ends_of_the_range(torch, scale):
     h.close()
     ref = np.diag(f / v)
     assert np.all(np.abs(got - ref) <= 4 * 2.0**-52 * np.abs(ref) + 2 * 2.0**-1074)
+
+
+# 320 chunks of 64 mocks are the last that every workgroup adds up for itself
+@pytest.mark.parametrize("nm", [20480, 20481, 20544])
+@pytest.mark.parametrize("nd", [1, 70])
+def test_many_mocks(torch, nm, nd):
+    """Against numpy; sums of nm terms in FP64, as the tolerances say."""
+    x = np.random.default_rng(nm + nd).standard_normal((nm, nd)) + 3.0
+    h = T.Handle(100.0, np.linspace(0.0, 10.0, 2), 0)
+    mean, cov = h.covariance(torch.from_numpy(x).cuda())
+    h.close()
+    d = x - x.mean(0)
+    ref, sd = d.T @ d / (nm - 1), np.sqrt((d * d).sum(0))
+    assert np.all(np.abs(mean.cpu().numpy() - x.mean(0)) <= (nm + 4) * 2.0**-53 * np.abs(x).max(0))
+    assert np.all(np.abs(cov.cpu().numpy() - ref) <= 4.0 * (nm + 4) * 2.0**-53 * np.outer(sd, sd) / (nm - 1))
