@@ -963,7 +963,7 @@ tpcf_status pair_chunk(tpcf_handle h, const Chunk& ch) {
     b.nfix = P<int>(h->d_flag) + 2;
     b.nfix_total = P<int>(h->d_flag) + 3;
     b.vol = P<double>(h->d_vol);
-    b.inv_vst = (float)h->inv_vst;
+    b.inv_vst = h->inv_vst;
     // the reach of the per-item candidate cut: the outer edge with a margin
     // of 1e-4 (relative), far above the FP32 rounding of the coordinates
     b.reach2 = (float)(h->edges[h->nb] * h->edges[h->nb] * (1.0 + 2e-4));

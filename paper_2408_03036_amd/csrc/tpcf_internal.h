@@ -118,7 +118,7 @@ struct BinArgs {
     int* nfix;               // [1] its length
     int* nfix_total;         // [1] the fix-up launches add the lengths they processed
     const double* vol;       // [nb] shell volumes
-    float inv_vst;           // 1 / stencil volume (the box in one-cell mode)
+    double inv_vst;          // 1 / stencil volume (the box in one-cell mode)
     float reach2;            // squared reach of a work item's candidate cut (outer edge, with a margin)
     int npmax;               // capacity of the piece table (>= 2 nruns)
     int uniform;             // bins equally spaced in r: bin = floor((r - e0) / dr)

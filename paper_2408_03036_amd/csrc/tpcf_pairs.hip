@@ -523,7 +523,12 @@ __device__ __forceinline__ void bin_item(const BinArgs& a, ItemCtx& c, Pieces& S
         if (c.wave == 0) {
             int cap = 0;
             if (lane < a.nb) {
-                const float pred = (float)c.total_full * (float)a.vol[lane] * a.inv_vst;
+                // The bin's share of the stencil's volume, formed in FP64:
+                // volumes leave the range of FP32 in boxes of 1e-12 and of
+                // 1e13 units, and what is not a number up to 1 must not
+                // become an index (no room then: the exact layout follows).
+                const float share = (float)(a.vol[lane] * a.inv_vst);
+                const float pred = share <= 1.0f ? (float)c.total_full * share : 0.0f;
                 // a multiple of four: the offsets count blocks of four slots
                 cap = ((int)ceilf(1.15f * pred + 4.0f * sqrtf(pred) + 8.0f) + 3) & ~3;
             }
