@@ -113,7 +113,7 @@ struct tpcf_handle_s {
     double hits_per_list = 0.0;  // predicted mean length of a (p, b) list
     double list_grow = 1.0;      // list room found needed beyond the prediction (doubles per overflow)
     double chunk_budget = 0.0;   // bytes of a chunk's operand and lists (0: half the workspace)
-    double chunk_bytes = 0.0;    // of the largest chunk planned
+    double chunk_bytes = 0.0;    // of the largest chunk planned that holds several subchunks
     bool full = false;           // an allocation did not fit
     unsigned long long list_cap = 0;
     DevBuf d_fix;
@@ -865,7 +865,7 @@ tpcf_status plan_chunks(tpcf_handle h) {
         ch.sub_end = s;
         ch.p_end = h->sub_start[s];
         max_room = std::max(max_room, r_acc);
-        h->chunk_bytes = std::max(h->chunk_bytes, b_acc);
+        if (ch.sub_end - ch.sub_begin > 1) h->chunk_bytes = std::max(h->chunk_bytes, b_acc);
         h->chunks.push_back(ch);
     }
     int64_t maxch = 0;
@@ -916,10 +916,11 @@ tpcf_status plan_chunks(tpcf_handle h) {
     return ensure(h, h->d_S, sizeof(double) * h->ncat * (part_doubles(h) - h->gsize));
 }
 
-// Plans chunks of half the largest one's bytes from here on, and gives back what
-// was sized for it. False where every chunk holds one subchunk already.
+// Plans chunks of half the bytes of the largest one that can be divided from
+// here on, and gives back what was sized for the present ones. False where
+// every chunk holds one subchunk already.
 bool shrink_chunks(tpcf_handle h) {
-    if (h->chunks.size() + 1 >= h->sub_start.size()) return false;
+    if (!(h->chunk_bytes > 0.0)) return false;
     for (DevBuf* b : {&h->d_boff, &h->d_fix, &h->d_cnt, &h->d_A, &h->d_list}) release(h, *b);
     h->chunk_budget = 0.5 * h->chunk_bytes;
     return true;

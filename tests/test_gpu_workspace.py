@@ -77,6 +77,19 @@ def test_contraction_of_wide_operands(torch, n, nb, lmax, prec, weighted):
     edges_of.test_contraction_of_exported_alm(torch, n, nb, lmax, prec, weighted)
 
 
+def test_no_room_at_all(torch):
+    """Catalogues of one and of four subchunks in a workspace below the
+    smallest lists (16 MB): refused, whatever the chunks."""
+    sizes = [256, 3, 3, 900, 3]
+    pos = torch.from_numpy(C.poisson(sum(sizes), 1.0, 5)).cuda()
+    h = T.Handle(1.0, np.linspace(0.05, 0.5, 4), 11, workspace_limit=10 << 20)
+    for _ in range(2):
+        with pytest.raises(T.TpcfError) as e:
+            h.run_catalogs(sizes, sizes, pos, None, [(0, 0, 0)])
+        assert e.value.status == T.TPCF_ERR_ALLOC
+    h.close()
+
+
 def test_crowded_cells_need_no_room(torch):
     """The arrays of a grid take 96 bytes per point and 4 per work item of 16
     points; the counters of a crowded cell's slabs (0.75 bytes per point) fit
