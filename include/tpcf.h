@@ -195,7 +195,7 @@ tpcf_status tpcf_multipoles(tpcf_handle h, int32_t n_mult, const int32_t* h_l1l2
  * multipole being orthogonal over m); the results equal those of steps 1-4 bit
  * for bit. Until the next tpcf_build_grid the handle then refuses, with
  * TPCF_ERR_STATE, a tpcf_contract export of NNN^m and tpcf_multipoles triples
- * with L > lmax. Likewise the split-BF16 contraction of such a run forms only
+ * with L > lmax. Likewise the contraction of such a run forms only
  * the (l1, l2) blocks that its multipoles couple (|l1 - l2| up to the largest
  * among them, each multipole needing |l1 - l2| <= L): until the next
  * tpcf_build_grid, triples with a larger |l1 - l2| and the per-m export are

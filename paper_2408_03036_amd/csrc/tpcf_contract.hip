@@ -272,7 +272,10 @@ __global__ void __launch_bounds__(64 * kF64Waves) k_contract_f64(ContractArgs a,
 // a lane reads four MFMAs' operands at once (row stride 36 floats: no bank
 // conflicts). With weights the columns stay bin-major and every tile is
 // formed: the weight multiplies the first column of a pair, and the rounding
-// of w x depends on which that is. PERF32
+// of w x depends on which that is.
+// 9e6 primaries in subchunks of 256, lmax 4 and 12 bins: 8.8 ms (1.7 TB/s of
+// operand); 30,011 at lmax 13 and 7 bins: 126 us. One buffer, a branch per tile
+// in the MFMA loop and subchunks of 4096 took 57.8 ms and 370 us.
 constexpr int kF32Waves = 8, kF32TPW = 2, kF32Stride = kUnit + 4;
 
 __host__ __device__ constexpr size_t f32_lds(int flat_cols, int units, int nbuf) {

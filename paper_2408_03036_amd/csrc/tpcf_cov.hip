@@ -29,8 +29,8 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 // chunk are read kMeanUnroll at a time and added in order (one load at a time
 // the sums alone took 18 us for 3000 x 336, most of it latency; gather and
 // sums together now take 10 us). An offset outside a row (possible only for offsets
-// given in device memory, which the host cannot check) reads nothing and
-// gives NaN.
+// given in device memory, which the host cannot check) reads the row's first
+// entry, drops it and gives NaN.
 constexpr int kMeanChunk = 64;
 constexpr int kMeanUnroll = 16;
 

@@ -153,7 +153,7 @@ struct AlmArgs {
     const float4* rec;       // hit records (dx, dy, dz, w_j) (FP32 paths)
     int unit_w;              // all weights are 1
     int wave_per_list;       // long lists: one wavefront per (p, b) list (FP32, lmax <= 6)
-    int self_lo;             // FP32 whole-m lanes: self moments only to order lmax (run asks for L <= lmax)
+    int self_lo;             // self moments only to order lmax (the run asks for L <= lmax)
     const uint32_t* boff;
     const uint32_t* cnt;
     void* A;                 // [nb][nvalues][ldA] float or double
@@ -245,9 +245,10 @@ struct ContractArgs {
     const int64_t* goff;     // [lmax+1] offset of G_m inside a partial
     int mode;                // 0 fp64, 1 fp32, 2 bf16x3, 3 bf16x6
     int unit_weights;        // all weights 1: skip the weight multiply
-    const float* pw;         // FP32 weights, sorted order (split-BF16 modes)
+    const float* pw;         // FP32 weights, sorted order (FP32 and split-BF16 modes)
     int ks_max;              // split-BF16: longest step in primaries (0: the longest that fits)
-    int lcouple;             // split-BF16: blocks with |l1 - l2| > lcouple may be skipped (>= lmax: none)
+    int lcouple;             // blocks with |l1 - l2| > lcouple may be skipped (>= lmax: none; FP32 with
+                             // weights and the isotropic schedule do not read it)
 };
 hipError_t launch_contract(const ContractArgs& a, hipStream_t s);
 // Isotropic schedule: only the l1 = l2 blocks of every G_m (nb <= 32); the
