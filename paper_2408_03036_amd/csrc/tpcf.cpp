@@ -899,8 +899,8 @@ tpcf_status plan_chunks(tpcf_handle h) {
     if ((st = ensure(h, h->d_boff, sizeof(uint32_t) * maxch * h->nb)) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_fix, sizeof(int) * 2 * maxch)) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_cnt, sizeof(uint32_t) * maxch * h->nb)) != TPCF_OK) return st;
-    // 8 elements of padding: the contraction's staging reads 8-wide windows
-    if ((st = ensure(h, h->d_A, ((size_t)h->nb * h->NV * h->ldA + 8) * elem)) != TPCF_OK) return st;
+    // 16 elements of padding: the contractions' staging reads 8- and 16-wide windows
+    if ((st = ensure(h, h->d_A, ((size_t)h->nb * h->NV * h->ldA + 16) * elem)) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_list, (size_t)list_elem_bytes(h) * h->list_cap)) != TPCF_OK) return st;
     if ((st = ensure(h, h->d_lcursor, sizeof(unsigned long long) * kSlots * 16)) != TPCF_OK) return st;
     // subchunk tables: chunk-relative starts of every chunk, one upload

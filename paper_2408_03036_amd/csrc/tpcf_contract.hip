@@ -417,14 +417,14 @@ __global__ void __launch_bounds__(64 * kF32Waves) k_contract_f32(ContractArgs a,
 //   G_m[(b1,l),(b2,l)] = sum_p w_p Re(A_lm(p,b1) conj(A_lm(p,b2))).
 // One wavefront per (subchunk, (l, m)) forms that nb x nb block on 16x16x4
 // MFMA in 16 x 16 tiles over (b1, b2) (up to 32 bins). A step covers 64
-// primaries from a 16-aligned start: lane (i, g) = (lane % 16, lane / 16)
+// primaries from the subchunk's first: lane (i, g) = (lane % 16, lane / 16)
 // loads 16 consecutive values of bin i (vector loads, masked to the subchunk)
 // and feeds 16 MFMAs, each summing four primaries, one per lane group. FP64
 // operands use FP64 MFMA; FP32 operands use FP32 MFMA, and the FP32 sums of
 // one step (16 products per entry and chain) go into FP64 registers.
 constexpr int kIsoWaves = 4;
 
-// 16 consecutive values of one row (16-aligned), kept in their storage type
+// 16 consecutive values of one row (at any alignment), kept in their storage type
 // until used: the next step's values are loaded while the current step's
 // MFMAs run.
 template <typename TA> struct Raw16;
@@ -432,18 +432,16 @@ typedef float fvec4 __attribute__((ext_vector_type(4)));
 template <> struct Raw16<float> {
     fvec4 v[4];
     __device__ __forceinline__ void load(const float* src) {
-        const fvec4* p = reinterpret_cast<const fvec4*>(src);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = p[q];
+        for (int q = 0; q < 4; ++q) __builtin_memcpy(&v[q], src + 4 * q, 16);
     }
     __device__ __forceinline__ double get(int k) const { return (double)v[k >> 2][k & 3]; }
 };
 template <> struct Raw16<double> {
     double2 v[8];
     __device__ __forceinline__ void load(const double* src) {
-        const double2* p = reinterpret_cast<const double2*>(src);
 #pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = p[q];
+        for (int q = 0; q < 8; ++q) __builtin_memcpy(&v[q], src + 2 * q, 16);
     }
     __device__ __forceinline__ double get(int k) const { return (k & 1) ? v[k >> 1].y : v[k >> 1].x; }
 };
@@ -479,13 +477,12 @@ __global__ void __launch_bounds__(64 * kIsoWaves) k_contract_iso(ContractArgs a)
 #pragma unroll
     for (int q = 0; q < 3; ++q) acc[q] = (f64x4)0.0;
 
-    // steps of 64 primaries from a 16-aligned start; rows are padded to ldA
-    // (a multiple of 64), so every 16-aligned group starting below pb is
-    // inside its row
-    const int64_t p00 = pa & ~(int64_t)15;
-    const int nsteps = (int)((pb - p00 + 63) / 64);
+    // Steps of 64 primaries from the subchunk's first, so that the sums do not
+    // depend on where it lies in the chunk; the operand ends with 16 elements of
+    // padding, so that every group starting below pb is inside it
+    const int nsteps = (int)((pb - pa + 63) / 64);
     const int nit = nsteps * parts;
-    auto group = [&](int it) { return p00 + (int64_t)(it / parts) * 64 + 16 * g; };
+    auto group = [&](int it) { return pa + (int64_t)(it / parts) * 64 + 16 * g; };
     // FP32 weights of a group are prefetched with its values (the weight
     // buffer ends with 16 floats of padding); FP64 reads them from the points
     constexpr bool F32 = std::is_same<TA, float>::value;
@@ -500,7 +497,7 @@ __global__ void __launch_bounds__(64 * kIsoWaves) k_contract_iso(ContractArgs a)
     // used covers only that set (a two-set ping-pong, no register rotation).
     auto fetch = [&](int it, Set& S) {
         int64_t q0 = group(it);
-        if (q0 >= pb) q0 = p00;
+        if (q0 >= pb) q0 = pa;
         const int64_t off = (it % parts) * pstep + q0;
         S.r0.load(A + row0 + off);
         if (nt > 1) S.r1.load(A + row1 + off);
@@ -523,14 +520,14 @@ __global__ void __launch_bounds__(64 * kIsoWaves) k_contract_iso(ContractArgs a)
         const Raw16<TA>& c0 = S.r0;
         const Raw16<TA>& c1 = S.r1;
         const int64_t q0 = group(it);
-        const int lo = (int)max<int64_t>(pa - q0, -1), hi = (int)min<int64_t>(pb - q0, 17);
+        const int hi = (int)max<int64_t>(0, min<int64_t>(pb - q0, 16));
         if constexpr (F32) {
             f32x4 sa[3], sb[3];
 #pragma unroll
             for (int q = 0; q < 3; ++q) sa[q] = sb[q] = (f32x4)0.0f;
 #pragma unroll
             for (int k = 0; k < 16; ++k) {
-                const bool in = k >= lo && k < hi;
+                const bool in = k < hi;
                 const float x0 = (in && ok0) ? c0.v[k >> 2][k & 3] : 0.0f;
                 const float wk = W ? (in ? S.w.v[k >> 2][k & 3] : 0.0f) : 1.0f;
                 const float wa0 = W ? x0 * wk : x0;
@@ -549,7 +546,7 @@ __global__ void __launch_bounds__(64 * kIsoWaves) k_contract_iso(ContractArgs a)
         } else {
 #pragma unroll
             for (int k = 0; k < 16; ++k) {
-                const bool in = k >= lo && k < hi;
+                const bool in = k < hi;
                 const double x0 = (in && ok0) ? c0.get(k) : 0.0;
                 const double wk = W ? (in ? a.pd[a.p_begin + q0 + k].w : 0.0) : 1.0;
                 const double wa0 = W ? x0 * wk : x0;

@@ -99,3 +99,21 @@ def test_crowded_cells_need_no_room(torch):
     h = T.Handle(100.0, np.linspace(10.0, 50.0, 3), 0, workspace_limit=int(96.5 * n))
     h.build_grid(pos)
     h.close()
+
+
+@pytest.mark.parametrize("prec", [T.PREC_FP64, T.PREC_FP32, T.PREC_MIXED_BF16X6])
+@pytest.mark.parametrize("nb,lmax", [(6, 4), (20, 6)])
+@pytest.mark.parametrize("weighted", [False, True])
+def test_isotropic_batches_equal_single_runs(torch, prec, nb, lmax, weighted):
+    """Bit for bit, for catalogues that begin anywhere in the batch."""
+    sizes = [257, 301, 515, 1000, 33]
+    pos = [torch.from_numpy(C.poisson(n, 100.0, 60 + n)).cuda() for n in sizes]
+    rng = np.random.default_rng(3)
+    w = [torch.from_numpy(rng.uniform(-1.0, 1.0, n)).cuda() if weighted else None for n in sizes]
+    mults = [(l, l, 0) for l in range(lmax + 1)]
+    h = T.Handle(100.0, np.linspace(2.0, 40.0, nb + 1), lmax, precision=prec, flags=T.F_ISOTROPIC)
+    many = h.run_catalogs(sizes, sizes, torch.cat(pos), torch.cat(w) if weighted else None, mults).cpu().numpy()
+    for c, n in enumerate(sizes):
+        one = h.run_catalogs([n], [n], pos[c], w[c], mults).cpu().numpy()
+        assert np.array_equal(one[0], many[c])
+    h.close()
