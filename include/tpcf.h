@@ -146,7 +146,8 @@ tpcf_status tpcf_build_grid(tpcf_handle h, const double* d_pos, const double* d_
  * the stream once, after the last chunk, to learn whether the hit lists ran
  * out of room (strong clustering), and then runs the pass again with twice
  * the room (which the handle keeps for later calls). TPCF_ERR_ALLOC when the
- * room cannot grow within the workspace limit or 16e9 entries.
+ * room cannot grow within 16e9 entries, or within the workspace limit with
+ * chunks of one subchunk (a pass that does not fit is tried in smaller chunks).
  */
 tpcf_status tpcf_alm_accumulate(tpcf_handle h);
 
